@@ -97,12 +97,13 @@ typedef struct gg_mask_params {
 /* Launch shape of the volume kernels (tsdf_integrate and its variants,
  * tsdf_extract_depth, gg_fusion_stream_probe), passed with each call; NULL or
  * a zero field takes the default.  Results never depend on it (it exists for
- * the autotuner).
+ * the autotuner).  The fusion's workgroup is fixed (64 target pixels, each
+ * lane 8 bins at a time): of the fields it takes band_width, the others shape
+ * tsdf_extract_depth.  bins_per_thread also sets the alignment that the
+ * volumes of either call must have (4 bytes times the bins taken).
  *   pixels_per_block  whole target pixels per workgroup, 0..1024 (0: 512
  *                     threads' worth)
- *   pixels_per_row    neighbouring pixels interleaved in a wavefront row of
- *                     the fusion, 0..64 (the largest power of two <= it
- *                     dividing pixels_per_block is used; 0: 16)
+ *   pixels_per_row    0..64 (no kernel takes it)
  *   bins_per_thread   1, 2, 4 or 8 (0: 4 where it divides num_bins); used
  *                     where it divides num_bins and, for 8, where every
  *                     volume argument is 32-byte aligned, else the largest of
@@ -114,7 +115,7 @@ typedef struct gg_mask_params {
  *                     share are still cached when the next row needs them;
  *                     0..65536 (0: 256); a band as wide as the target is
  *                     plain row-major order, which is also taken where the
- *                     target width is not a multiple of pixels_per_block.
+ *                     target width is not a multiple of 64.
  * Invalid values: GG_ERR_INVALID. */
 typedef struct gg_volume_tuning {
   int32_t pixels_per_block;
@@ -374,6 +375,9 @@ int difference_masks(int32_t K, int32_t width, int32_t height, const uint8_t *rg
  * alias F, W.  F, W float tgt_h x tgt_w x D: overwritten.
  * out_depth float tgt_h x tgt_w, out_bin int32 tgt_h x tgt_w: both or neither.
  * tuning [host]: the launch shape, or NULL (gg_volume_tuning).
+ * ws: gg_workspace_size(GG_OP_TSDF_INTEGRATE, ...).  Its last part, 8 K
+ * ceil(src_w / 32) ceil(src_h / 32) bytes rounded up to 256, only speeds the
+ * call up: a workspace without it is taken too, with the same results.
  * ------------------------------------------------------------------------- */
 int tsdf_integrate(const gg_camera *src, int32_t K, const float *depth, const gg_camera *tgt,
                    const gg_tsdf_params *prm, const float *temporal_mask, const float *F_prev,
@@ -387,8 +391,8 @@ int tsdf_integrate(const gg_camera *src, int32_t K, const float *depth, const gg
  * confidence of the supplement), and the bin depths; tsdf_integrate_tabled
  * then fuses from that ws exactly as tsdf_integrate does (bitwise the same
  * outputs).  Arguments as tsdf_integrate; both calls take the same src, K,
- * prm and ws (gg_workspace_size(GG_OP_TSDF_INTEGRATE, ...)); the caller
- * orders them (one stream, or an event) and keeps ws untouched between. */
+ * prm, ws and ws_bytes (gg_workspace_size(GG_OP_TSDF_INTEGRATE, ...)); the
+ * caller orders them (one stream, or an event) and keeps ws untouched between. */
 int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
                     const gg_tsdf_params *prm, void *ws, size_t ws_bytes, void *stream);
 int tsdf_integrate_tabled(const gg_camera *src, int32_t K, const gg_camera *tgt,
@@ -403,9 +407,9 @@ int tsdf_integrate_tabled(const gg_camera *src, int32_t K, const gg_camera *tgt,
  * and errors are those of tsdf_integrate (bitwise the same outputs); the
  * scratch (the view table and the bin table) is a static device array of the
  * library, GG_NOALLOC_SCRATCH_BYTES (64 MiB) per device, held from the first
- * call on a device until the process ends.  A call whose workspace would
- * exceed it (gg_workspace_size(GG_OP_TSDF_INTEGRATE, ...) > 64 MiB, e.g.
- * more than about 8.3 M source pixels over all views) returns
+ * call on a device until the process ends.  A call whose workspace (without
+ * its last part, see tsdf_integrate) would exceed it, e.g. of more than about
+ * 8.3 M source pixels over all views, returns
  * GG_ERR_UNSUPPORTED before anything is enqueued.  Every call on one device
  * shares that device's scratch, which keeps the last call's contents and is
  * fully rewritten before it is read: calls that overlap on one device (other
@@ -479,15 +483,14 @@ typedef struct gg_batch_item {
   float *sp_depth, *sp_rgb, *sp_alpha;
   float *sp_tape;               /* or NULL                                           */
   gg_volume_tuning volume;      /* this item's fusion launch shape, as tsdf_integrate
-                                   takes it (all 0: the plan's pixels_per_block and
-                                   bins_per_thread, bands of 256 pixels); invalid
-                                   values fail the plan with GG_ERR_INVALID         */
+                                   takes it (all 0: the plan's bins_per_thread, bands
+                                   of 256 pixels); invalid values fail the plan with
+                                   GG_ERR_INVALID                                   */
 } gg_batch_item;
 
 /* Launch shape chosen by the autotuner (0 = default). */
 typedef struct gg_batch_tuning {
-  int32_t pixels_per_block; /* target pixels per fusion workgroup, 0..1024 (0: 16; fewer
-                               where the workgroup would exceed 1024 threads)             */
+  int32_t pixels_per_block; /* 0..1024 (the fusion's workgroups hold 64 pixels)            */
   int32_t blocks_per_cu;   /* resident workgroups per compute unit of the persistent splat
                               binning phases, 0..64 (0: as many as fit)                    */
   int32_t bins_per_thread; /* of the fusion, as in gg_volume_tuning (0: default)            */

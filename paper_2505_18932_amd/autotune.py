@@ -5,14 +5,11 @@ the time does.  The tuner times candidates on the device with HIP events and
 caches the winner per GPU architecture and workload class in a JSON file
 next to this module (``tuning_cache.json``):
 
-* plain path: bins per thread, pixels per workgroup and per wavefront row of
-  the fusion and the band width of its tile order for a (K, D, width, height)
-  class: a launch shape the caller
-  passes with each call (``tuning=`` of the volume calls, the C ABI's
+* plain path: the band width of the fusion's tile order for a (K, D, width,
+  height) class: a launch shape the caller passes with each call (``tuning=`` of the volume calls, the C ABI's
   ``gg_volume_tuning``); nothing is set process-wide;
-* batched path: (pixels per fusion workgroup, resident workgroups per
-  compute unit of the persistent splat binning, bins per thread, graph
-  branches) for a batch signature.
+* batched path: (resident workgroups per compute unit of the persistent splat
+  binning, graph branches) for a batch signature.
 """
 from __future__ import annotations
 
@@ -28,16 +25,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CACHE = os.path.join(HERE, "tuning_cache.json")
 
 # (pixels per workgroup, pixels per wavefront row, bins per thread, band width of the tile
-# order in pixels); 0 = default
-PLAIN_CANDIDATES = [(0, 0, 4, 0), (8, 8, 4, 0), (16, 8, 4, 0), (16, 16, 4, 0), (32, 8, 4, 0),
-                    (32, 16, 4, 0), (0, 0, 8, 0), (16, 16, 8, 0), (32, 16, 8, 0), (32, 32, 8, 0),
-                    (64, 16, 8, 0), (64, 32, 8, 0), (16, 16, 8, 128), (16, 16, 8, 192),
-                    (16, 16, 8, 512), (16, 16, 8, 65536), (32, 16, 8, 128)]
-# (target pixels per fusion workgroup, resident workgroups per compute unit of
-# the persistent splat binning phases, bins per thread, graph branches);
-# 0 = default
-BATCH_CANDIDATES = [(16, 0, 8, 2), (16, 0, 8, 1), (32, 0, 8, 2), (16, 1, 8, 2), (16, 2, 8, 2),
-                    (16, 0, 4, 2), (32, 0, 4, 2)]
+# order in pixels); 0 = default.  The fusion's workgroup is fixed: its candidates are bands.
+PLAIN_CANDIDATES = [(0, 0, 0, 0), (0, 0, 0, 64), (0, 0, 0, 128), (0, 0, 0, 192), (0, 0, 0, 512),
+                    (0, 0, 0, 65536)]
+# (pixels per fusion workgroup, resident workgroups per compute unit of the
+# persistent splat binning phases, bins per thread, graph branches); 0 = default
+BATCH_CANDIDATES = [(0, 0, 0, 2), (0, 0, 0, 1), (0, 1, 0, 2), (0, 2, 0, 2)]
 
 
 def arch(device=None) -> str:
@@ -75,7 +68,7 @@ def _time(fn, reps=5, warm=2):
 
 
 def plain_key(K, D, width, height):
-    return f"plain-b/K{K}/D{D}/{width}x{height}"
+    return f"plain-s/K{K}/D{D}/{width}x{height}"
 
 
 def tune_plain(src, depth, tgt, params, reps=5, use_cache=True):
@@ -133,7 +126,7 @@ def batch_signature(items):
     sig = sorted((len(it["src"]), ops.tsdf_params(it["tsdf"]).num_bins,
                   ops.camera(it["tgt"]).width, ops.camera(it["tgt"]).height,
                   it.get("rgb") is not None, own(it)) for it in items)
-    return "batch-v/" + ";".join("K%dD%d/%dx%d/%d%s" % s for s in sig)
+    return "batch-s/" + ";".join("K%dD%d/%dx%d/%d%s" % s for s in sig)
 
 
 def tune_batch(items, reps=3, use_cache=True):

@@ -301,9 +301,12 @@ static EwaLayout ewa_layout(int K, int sw, int sh, int tw, int th, const gg_spla
 }
 
 struct TsdfLayout {
-  size_t table, bins, acc, gnu, total;
+  size_t table, bins, cells, acc, gnu, base, total;
+  uint32_t ncells;
 };
 
+// base: what every call needs; total: with the cells' depth ranges, which only speed the fusion up
+// (a workspace of base bytes is taken without them).
 static TsdfLayout tsdf_layout(int K, int sw, int sh, int D, bool backward) {
   TsdfLayout L{};
   const size_t ns = (size_t)sw * sh;
@@ -317,6 +320,12 @@ static TsdfLayout tsdf_layout(int K, int sw, int sh, int D, bool backward) {
     o += up256(8 * (2 * ns * K + 1));
     L.gnu = o;
     o += up256(4 * ns * K);
+  }
+  L.base = o;
+  if (!backward) {
+    L.cells = o;
+    L.ncells = (uint32_t)K * cells_across(sw) * cells_across(sh);
+    o += up256(8 * (size_t)L.ncells);
   }
   L.total = o;
   return L;
@@ -350,32 +359,26 @@ static int check_tuning(const gg_volume_tuning *t, const char *what) {
 
 struct VolumeShape {
   int V;
-  uint32_t cpp, ppb, threads, nblocks, pw_shift;
-  uint32_t band_px;  // fusion tile order: band width in target pixels
+  uint32_t cpp, ppb, threads, nblocks;
 };
 
 constexpr uint32_t kDefaultBandPixels = 256;
+static uint32_t band_pixels(const gg_volume_tuning *t) {
+  return t && t->band_width > 0 ? (uint32_t)t->band_width : kDefaultBandPixels;
+}
 
 // The fusion's tile order (IntegrateArgs::band_*) for a target of width x
-// height pixels in tiles of ppb pixels: bands of band_px pixels across where
-// whole tiles make up each row, else row-major.
-static void set_band_order(IntegrateArgs &a, int width, int height, uint32_t ppb,
-                           uint32_t band_px) {
+// height pixels: bands of band_px pixels across where whole tiles make up
+// each row, else row-major.
+static void set_band_order(IntegrateArgs &a, int width, int height, uint32_t band_px) {
   a.band_T = a.band_B = a.band_H = 0;
-  if ((uint32_t)width % ppb != 0) return;
-  const uint32_t T = (uint32_t)width / ppb;
-  const uint32_t B = std::max(1u, band_px / ppb);
+  if ((uint32_t)width % kFusePix != 0) return;
+  const uint32_t T = (uint32_t)width / kFusePix;
+  const uint32_t B = std::max(1u, band_px / kFusePix);
   if (B >= T) return;
   a.band_T = T;
   a.band_B = B;
   a.band_H = (uint32_t)height;
-}
-
-// Largest power of two <= cap (and <= 64) dividing ppb, as a shift.
-static uint32_t pick_pw_shift(uint32_t ppb, int cap) {
-  uint32_t sh = 0;
-  while ((2u << sh) <= (uint32_t)cap && (2u << sh) <= 64u && ppb % (2u << sh) == 0) ++sh;
-  return sh;
 }
 
 // Bins per thread: the tuning's choice where it divides D (and, for 8, the
@@ -389,7 +392,6 @@ static int volume_shape(int D, uint32_t npix, VolumeShape &s, const char *what,
                         bool aligned32, const gg_volume_tuning *tun) {
   if (int rc = check_tuning(tun, what)) return rc;
   const int ppb_t = tun ? tun->pixels_per_block : 0;
-  const int pw_t = tun ? tun->pixels_per_row : 0;
   s.V = volume_v(D, aligned32, tun ? tun->bins_per_thread : 0);
   s.cpp = (uint32_t)(D / s.V);
   if (s.cpp > 1024) return fail(GG_ERR_UNSUPPORTED, "%s: D = %d too large", what, D);
@@ -399,8 +401,6 @@ static int volume_shape(int D, uint32_t npix, VolumeShape &s, const char *what,
   s.ppb = ppb;
   s.threads = ppb * s.cpp;
   s.nblocks = (npix + ppb - 1) / ppb;
-  s.pw_shift = pick_pw_shift(ppb, pw_t > 0 ? pw_t : 16);
-  s.band_px = (tun && tun->band_width > 0) ? (uint32_t)tun->band_width : kDefaultBandPixels;
   return GG_OK;
 }
 
@@ -724,11 +724,13 @@ static bool fast_reciprocal_safe(const Proj *views, int32_t K, const gg_camera &
   return true;
 }
 
-static ConfArgs conf_args(const float *depth, float2 *table, int sw, int sh, int K,
+static ConfArgs conf_args(const float *depth, float2 *table, uint32_t *cells, int sw, int sh, int K,
                           const gg_tsdf_params *p) {
   ConfArgs c{};
   c.depth = depth;
   c.table = table;
+  c.cells = cells;
+  c.ncells = (uint32_t)K * cells_across(sw) * cells_across(sh);
   c.Ws = sw;
   c.Hs = sh;
   c.K = K;
@@ -739,15 +741,33 @@ static ConfArgs conf_args(const float *depth, float2 *table, int sw, int sh, int
   return c;
 }
 
+// Rounding bounds of find_live for view P over a target of w x h pixels up to depth z_far: of
+// each homogeneous coordinate, 2^-21 of the magnitudes it is formed from (its fused multiply-adds
+// round three times, by at most 2^-24 of those each).  False where a bound is not small enough
+// for the test's own arithmetic.
+static bool view_slack(const Proj &P, const gg_camera &tgt, float z_far, float *slack) {
+  for (int r = 0; r < 3; ++r) {
+    const double h = std::fabs((double)P.H[3 * r]) * tgt.width +
+                     std::fabs((double)P.H[3 * r + 1]) * tgt.height +
+                     std::fabs((double)P.H[3 * r + 2]);
+    const double e = std::ldexp((double)z_far * 1.01 * h + std::fabs((double)P.c[r]), -21);
+    if (!(e < std::ldexp(1.0, 20))) return false;
+    slack[r] = (float)(e * 1.0001);
+  }
+  return true;
+}
+
+// cells: the cells' depth ranges built with the table, or null.
 static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t K,
-                                const gg_camera &tgt, const gg_tsdf_params &prm,
-                                const VolumeShape &vs, const float2 *table, const float2 *bins,
+                                const gg_camera &tgt, const gg_tsdf_params &prm, uint32_t band_px,
+                                const float2 *table, const float2 *bins, const float *cells,
                                 const float *mask, const float *F_prev, const float *W_prev,
                                 float *F, float *W, float *out_depth, int32_t *out_bin) {
   fill_views(src, K, &tgt, a.views);
-  const int sw = src[0].width, sh = src[0].height;
   a.table = table;
   a.bins = bins;
+  a.cells = cells;
+  a.ncells = K ? (uint32_t)K * cells_across(src[0].width) * cells_across(src[0].height) : 0u;
   a.mask = mask;
   a.F_prev = F_prev;
   a.W_prev = W_prev;
@@ -756,27 +776,25 @@ static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t 
   a.out_depth = out_depth;
   a.out_bin = out_bin;
   a.K = K;
-  a.Ws = sw;
-  a.Hs = sh;
+  a.Ws = K ? src[0].width : 1;
+  a.Hs = K ? src[0].height : 1;
   a.D = prm.num_bins;
   a.npix = (uint32_t)(tgt.width * tgt.height);
-  a.ns = (uint32_t)(sw * sh);
   a.wt_div = make_fastdiv((uint32_t)tgt.width);
-  a.cpp_div = make_fastdiv(vs.cpp);
-  a.cpp = vs.cpp;
-  a.ppb = vs.ppb;
-  a.pw_shift = vs.pw_shift;
-  a.nblocks = vs.nblocks;
-  set_band_order(a, tgt.width, tgt.height, vs.ppb, vs.band_px);
+  a.nblocks = (a.npix + kFusePix - 1) / kFusePix;
+  set_band_order(a, tgt.width, tgt.height, band_px);
   a.decay = prm.decay;
   a.cap = prm.weight_cap;
-  a.carry = F_prev != nullptr;
   a.exact_only = fast_reciprocal_safe(a.views, K, tgt, prm.z_far) ? 0 : 1;
-  // Structured view-table loads take three vector instructions per sample off the carried
-  // fusion, whose issue slots bound it at up to four views; at more views the texture address
-  // unit is the tighter bound and they lose, and the forms without a carry would lose a
-  // wavefront per SIMD to the extra address registers (measured; results are the same).
-  a.rows = (table_rows_ok(sw) && F_prev != nullptr && K <= 4) ? 1 : 0;
+  a.test = K > 0 && !a.exact_only;
+  a.zfar = prm.z_far * 1.01f;
+  for (int k = 0; k < K && a.test; ++k)
+    a.test = view_slack(a.views[k], tgt, prm.z_far, a.slack[k]) ? 1 : 0;
+}
+
+// The cells' place in a workspace of ws_bytes (null if it ends before them).
+static uint32_t *cells_of(const TsdfLayout &L, char *w, size_t ws_bytes) {
+  return ws_bytes >= L.total ? (uint32_t *)(w + L.cells) : nullptr;
 }
 
 // The view table (per source pixel: usable depth, fusion weight) and the
@@ -784,10 +802,10 @@ static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t 
 // depth maps only.
 static int build_view_table(const gg_camera *src, int32_t K, const float *depth,
                             const gg_tsdf_params *prm, const TsdfLayout &L, char *w,
-                            hipStream_t s) {
+                            uint32_t *cells, hipStream_t s) {
   const int sw = src[0].width, sh = src[0].height;
-  if (int rc = launch_bins(*prm, (float2 *)(w + L.bins), s)) return rc;
-  return launch_conf(conf_args(depth, (float2 *)(w + L.table), sw, sh, K, prm), s);
+  if (int rc = launch_bins(*prm, (float2 *)(w + L.bins), cells, cells ? L.ncells : 0u, s)) return rc;
+  return launch_conf(conf_args(depth, (float2 *)(w + L.table), cells, sw, sh, K, prm), s);
 }
 
 int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
@@ -797,8 +815,9 @@ int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
   if (int rc = check_tsdf(prm, N)) return rc;
   if (!depth) return fail(GG_ERR_INVALID, "%s: NULL array argument", N);
   const TsdfLayout L = tsdf_layout(K, src[0].width, src[0].height, prm->num_bins, false);
-  if (int rc = check_ws(ws, ws_bytes, L.total, N)) return rc;
-  return build_view_table(src, K, depth, prm, L, (char *)ws, (hipStream_t)stream);
+  if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
+  return build_view_table(src, K, depth, prm, L, (char *)ws, cells_of(L, (char *)ws, ws_bytes),
+                          (hipStream_t)stream);
 }
 
 // depth NULL: the view table and bins are already in ws (tsdf_view_table).
@@ -828,17 +847,18 @@ static int integrate_impl(const char *N, bool tabled, const gg_camera *src, int3
     return fail(GG_ERR_INVALID, "%s: volumes must be %zu-byte aligned", N, va);
   if ((size_t)npix * D > (size_t)1 << 40) return fail(GG_ERR_UNSUPPORTED, "%s: volume too large", N);
   const TsdfLayout L = tsdf_layout(K, sw, sh, D, false);
-  if (int rc = check_ws(ws, ws_bytes, L.total, N)) return rc;
+  if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
   hipStream_t s = (hipStream_t)stream;
   char *w = (char *)ws;
   float2 *table = (float2 *)(w + L.table);
   float2 *bins = (float2 *)(w + L.bins);
+  uint32_t *cells = cells_of(L, w, ws_bytes);
   if (!tabled)
-    if (int rc = build_view_table(src, K, depth, prm, L, w, s)) return rc;
+    if (int rc = build_view_table(src, K, depth, prm, L, w, cells, s)) return rc;
   IntegrateArgs a{};
-  make_integrate_args(a, src, K, *tgt, *prm, vs, table, bins, temporal_mask, F_prev, W_prev, F, W,
-                      out_depth, out_bin);
-  return launch_integrate(a, vs.V, vs.threads, s);
+  make_integrate_args(a, src, K, *tgt, *prm, band_pixels(tuning), table, bins, (const float *)cells,
+                      temporal_mask, F_prev, W_prev, F, W, out_depth, out_bin);
+  return launch_integrate(a, s);
 }
 
 int tsdf_integrate(const gg_camera *src, int32_t K, const float *depth, const gg_camera *tgt,
@@ -877,38 +897,17 @@ int gg_fusion_stream_probe(const gg_camera *tgt, const gg_tsdf_params *prm,
     return fail(GG_ERR_INVALID, "%s: volumes must be %zu-byte aligned", N, va);
   if ((size_t)npix * D > (size_t)1 << 40) return fail(GG_ERR_UNSUPPORTED, "%s: volume too large", N);
   const TsdfLayout L = tsdf_layout(1, 1, 1, D, false);
-  if (int rc = check_ws(ws, ws_bytes, L.total, N)) return rc;
+  if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
   hipStream_t s = (hipStream_t)stream;
   float2 *bins = (float2 *)((char *)ws + L.bins);
-  if (int rc = launch_bins(*prm, bins, s)) return rc;
+  if (int rc = launch_bins(*prm, bins, nullptr, 0, s)) return rc;
   // the fusion kernel's own launch with no views: every voxel only decays
   // its carried weight (W = min(decay W_prev, cap), F = that weight times
   // F_prev over itself), so the kernel moves exactly its volume stream
   IntegrateArgs a{};
-  a.table = (const float2 *)ws;
-  a.bins = bins;
-  a.F_prev = F_prev;
-  a.W_prev = W_prev;
-  a.F = F;
-  a.W = W;
-  a.out_depth = out_depth;
-  a.out_bin = out_bin;
-  a.K = 0;
-  a.Ws = a.Hs = 1;
-  a.D = D;
-  a.npix = npix;
-  a.ns = 1;
-  a.wt_div = make_fastdiv((uint32_t)tgt->width);
-  a.cpp_div = make_fastdiv(vs.cpp);
-  a.cpp = vs.cpp;
-  a.ppb = vs.ppb;
-  a.pw_shift = vs.pw_shift;
-  a.nblocks = vs.nblocks;
-  a.decay = prm->decay;
-  a.cap = prm->weight_cap;
-  a.carry = 1;
-  a.exact_only = 0;
-  return launch_integrate(a, vs.V, vs.threads, s);
+  make_integrate_args(a, nullptr, 0, *tgt, *prm, band_pixels(tuning), (const float2 *)ws, bins,
+                      nullptr, nullptr, F_prev, W_prev, F, W, out_depth, out_bin);
+  return launch_integrate(a, s);
 }
 
 int tsdf_integrate_noalloc(const gg_camera *src, int32_t K, const float *depth,
@@ -919,7 +918,7 @@ int tsdf_integrate_noalloc(const gg_camera *src, int32_t K, const float *depth,
   const char *N = "tsdf_integrate_noalloc";
   if (int rc = check_sources(src, K, N)) return rc;
   if (int rc = check_tsdf(prm, N)) return rc;
-  const size_t need = tsdf_layout(K, src[0].width, src[0].height, prm->num_bins, false).total;
+  const size_t need = tsdf_layout(K, src[0].width, src[0].height, prm->num_bins, false).base;
   if (need > kScratchBytes)
     return fail(GG_ERR_UNSUPPORTED, "%s: needs %zu bytes of scratch, the static scratch holds %zu",
                 N, need, kScratchBytes);
@@ -944,10 +943,10 @@ int tsdf_raymarch(const gg_camera *src, int32_t K, const float *depth, const gg_
     return fail(GG_ERR_INVALID, "%s: temporal_mask needs depth_prev and acc_prev", N);
   const int sw = src[0].width, sh = src[0].height, D = prm->num_bins;
   const TsdfLayout L = tsdf_layout(K, sw, sh, D, false);
-  if (int rc = check_ws(ws, ws_bytes, L.total, N)) return rc;
+  if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
   hipStream_t s = (hipStream_t)stream;
   float2 *table = (float2 *)((char *)ws + L.table);
-  if (int rc = launch_conf(conf_args(depth, table, sw, sh, K, prm), s)) return rc;
+  if (int rc = launch_conf(conf_args(depth, table, nullptr, sw, sh, K, prm), s)) return rc;
   RaymarchArgs a{};
   fill_views(src, K, tgt, a.views);
   a.table = table;
@@ -1122,8 +1121,8 @@ int tsdf_integrate_backward(const gg_camera *src, int32_t K, const float *depth,
   char *w = (char *)ws;
   float2 *table = (float2 *)(w + L.table);
   float2 *bins = (float2 *)(w + L.bins);
-  if (int rc = launch_bins(*prm, bins, s)) return rc;
-  if (int rc = launch_conf(conf_args(depth, table, sw, sh, K, prm), s)) return rc;
+  if (int rc = launch_bins(*prm, bins, nullptr, 0, s)) return rc;
+  if (int rc = launch_conf(conf_args(depth, table, nullptr, sw, sh, K, prm), s)) return rc;
   TsdfBackArgs a{};
   fill_views(src, K, tgt, a.views);
   const size_t ns = (size_t)sw * sh;
@@ -1216,10 +1215,6 @@ struct gg_batch {
   std::vector<char> keep;  // nothing host-side is needed after creation
 };
 
-// Target pixels per fusion workgroup of a batch item by default (as the plain
-// call's tuned launch shape takes them).
-constexpr uint32_t kBatchPixelsPerBlock = 16;
-
 // Bins per thread of a batch item (as for the plain call with that tuning).
 static bool item_aligned32(const gg_batch_item &it) {
   return aligned(it.F, 32) && aligned(it.W, 32) &&
@@ -1291,40 +1286,23 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
   // host descriptors, work lists and the device-memory layout
   std::vector<BatchItem> h(n);
   std::vector<WorkItem> conf, bin, raster;
-  std::vector<IntegGroup> groups;              // fusion launches: (class, workgroup size)
+  std::vector<IntegGroup> groups;              // fusion launches: (form, workgroup size)
   std::vector<std::vector<WorkItem>> integ;    // their work lists
   std::vector<uint32_t> splat_items;
-  std::vector<VolumeShape> shapes(n);
   std::vector<SplatLayout> sl(n);
   size_t off = up256(sizeof(BatchItem) * n);
-  std::vector<size_t> o_table(n), o_bins(n), o_splat(n);
+  std::vector<size_t> o_table(n), o_bins(n), o_cells(n), o_splat(n);
   size_t count_words = 0;
   std::vector<size_t> o_count(n);
   for (int i = 0; i < n; ++i) {
     const gg_batch_item &it = items[i];
     const int sw = it.src[0].width, sh = it.src[0].height, K = it.K, D = it.tsdf.num_bins;
-    const uint32_t npix = (uint32_t)(it.tgt.width * it.tgt.height);
-    VolumeShape &vs = shapes[i];
-    if (item_tuned(it)) {
-      // the item's own launch shape, exactly as tsdf_integrate would take it
-      char what[64];
-      snprintf(what, sizeof what, "%s: item %d", N, i);
-      if (int rc = volume_shape(D, npix, vs, what, item_aligned32(it), &it.volume)) return rc;
-    } else {
-      vs.V = item_vec(it, vec);
-      vs.cpp = (uint32_t)(D / vs.V);
-      // pixels per workgroup as the plain call's launch shape would give them
-      vs.ppb = ppb_t > 0 ? (uint32_t)ppb_t : kBatchPixelsPerBlock;
-      while (vs.ppb > 1 && vs.ppb * vs.cpp > 1024) --vs.ppb;
-      vs.threads = vs.ppb * vs.cpp;
-      vs.nblocks = (npix + vs.ppb - 1) / vs.ppb;
-      vs.pw_shift = pick_pw_shift(vs.ppb, 16);
-      vs.band_px = kDefaultBandPixels;
-    }
     o_table[i] = off;
     off += up256(8 * table_view_records(sw, sh) * K);
     o_bins[i] = off;
     off += up256(8 * (size_t)D);
+    o_cells[i] = off;
+    off += up256(8 * (size_t)K * cells_across(sw) * cells_across(sh));
     if (it.rgb) {
       if ((size_t)K * sw * sh * splat_tiles_per_splat(it.splat.r_max_px) > 0xffffffffull)
         return fail(GG_ERR_UNSUPPORTED, "%s: item %d has too many source pixels", N, i);
@@ -1351,31 +1329,21 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
           raster.push_back(WorkItem{(uint16_t)i, (uint16_t)k, (uint16_t)(t & 0xffff), (uint16_t)(t >> 16)});
       }
     }
-    IntegrateArgs probe{};  // only for the view count class and the reciprocal's range
-    make_integrate_args(probe, it.src, it.K, it.tgt, it.tsdf, vs, nullptr, nullptr, nullptr,
-                        nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
-    // the volume stream through LDS where the plain call would take it too
-    size_t stage_bytes = 0;
-    if (vs.threads % 64 == 0 && vs.pw_shift == 4 && vs.cpp % 4 == 0) {
-      if (vs.V == 8) stage_bytes = integrate_lds_bytes<8>(vs.threads, vs.ppb, D, true);
-      if (vs.V == 4) stage_bytes = integrate_lds_bytes<4>(vs.threads, vs.ppb, D, true);
-      if (stage_bytes > 65536) stage_bytes = 0;
-    }
-    const int mode = stage_bytes ? (it.F_prev ? 2 : 1) : 0;
-    const int cls = integ_class(vs.V, K, probe.exact_only != 0, mode);
+    IntegrateArgs probe{};  // the item's form and tile order
+    make_integrate_args(probe, it.src, it.K, it.tgt, it.tsdf, band_pixels(&it.volume), nullptr,
+                        nullptr, nullptr, nullptr, it.F_prev, it.W_prev, it.F, it.W, nullptr, nullptr);
+    const int form = integrate_form(probe), waves = fuse_waves(D, 1u << 20, form_direct(form));
     size_t gi = 0;
-    while (gi < groups.size() && !(groups[gi].cls == cls && groups[gi].threads == vs.threads)) ++gi;
+    while (gi < groups.size() && !(groups[gi].form == form && groups[gi].waves == waves)) ++gi;
     if (gi == groups.size()) {
       IntegGroup g;
-      g.cls = cls;
-      g.threads = vs.threads;
+      g.form = form;
+      g.waves = waves;
       groups.push_back(g);
       integ.emplace_back();
     }
-    groups[gi].shm = std::max(groups[gi].shm,
-                              stage_bytes ? stage_bytes : integrate_lds_head(vs.threads, vs.ppb));
     // the item's tiles in the plain launch's visiting order (bands)
-    for (uint32_t s = 0; s < vs.nblocks; ++s) {
+    for (uint32_t s = 0; s < probe.nblocks; ++s) {
       const uint32_t t = band_tile(probe, s);
       integ[gi].push_back(WorkItem{(uint16_t)i, 0, (uint16_t)(t & 0xffff), (uint16_t)(t >> 16)});
     }
@@ -1407,9 +1375,10 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
     const int sw = it.src[0].width, sh = it.src[0].height;
     float2 *table = (float2 *)(dv + o_table[i]);
     float2 *bins = (float2 *)(dv + o_bins[i]);
-    d.conf = conf_args(it.depth, table, sw, sh, it.K, &it.tsdf);
-    make_integrate_args(d.integ, it.src, it.K, it.tgt, it.tsdf, shapes[i], table, bins,
-                        it.temporal_mask, it.F_prev, it.W_prev, it.F, it.W, it.out_depth,
+    uint32_t *cells = (uint32_t *)(dv + o_cells[i]);
+    d.conf = conf_args(it.depth, table, cells, sw, sh, it.K, &it.tsdf);
+    make_integrate_args(d.integ, it.src, it.K, it.tgt, it.tsdf, band_pixels(&it.volume), table,
+                        bins, (const float *)cells, it.temporal_mask, it.F_prev, it.W_prev, it.F, it.W, it.out_depth,
                         it.out_bin);
     if (it.rgb) {
       make_splat_args(d.splat, it.src, it.K, it.depth, it.rgb, it.tgt, it.splat, sl[i],

@@ -28,14 +28,10 @@ __global__ void batch_zero_kernel(uint32_t *p, size_t n) {
 
 __global__ void batch_bins_kernel(const BatchItem *__restrict__ items) {
   const BatchItem &it = items[blockIdx.x];
-  for (int d = threadIdx.x; d < it.D; d += blockDim.x) {
-    const float un = 1.0f / it.z_near;
-    const float uf = 1.0f / it.z_far;
-    const float du = (un - uf) / (float)(it.D - 1);
-    const float u = un - (float)d * du;
-    const float z = 1.0f / u;
-    gstore2(it.bins + d, make_float2(z, it.trunc_in_bins ? (it.trunc * du) * (z * z) : it.trunc));
-  }
+  for (uint32_t d = threadIdx.x; d < padded_bins(it.D); d += blockDim.x)
+    gstore2(it.bins + d, bin_record((int)d, it.D, it.z_near, it.z_far, it.trunc, it.trunc_in_bins));
+  for (uint32_t c = threadIdx.x; c < 2 * it.conf.ncells; c += blockDim.x)
+    gmem(it.conf.cells)[c] = cell_start(c, it.conf.ncells);
 }
 
 // Dynamic work distribution in chunks, XCD-aware.  Entries differ in cost by
@@ -134,38 +130,23 @@ __global__ __launch_bounds__(256) void batch_raster_kernel(const BatchItem *__re
 }
 
 // Fusion: one workgroup tile of one item per work entry, every entry of a
-// launch in the same specialisation as the plain kernel (so the same code);
-// each item's tiles are listed in the plain launch's band order.
-template <int V, int KC, bool kExact, int kMode>
-__global__ __launch_bounds__(1024) void batch_integrate_kernel(const BatchItem *__restrict__ items,
-                                                               const WorkItem *__restrict__ work,
-                                                               uint32_t n) {
-  extern __shared__ float smem[];
+// launch in the same form of the plain kernel (so the same code); each
+// item's tiles are listed in the plain launch's band order.
+template <int kForm>
+__global__ __launch_bounds__(64 * kFuseMaxWaves) void batch_integrate_kernel(
+    const BatchItem *__restrict__ items, const WorkItem *__restrict__ work, uint32_t n) {
+  extern __shared__ __align__(16) float smem[];
   const WorkItem wi = uniform_entry(work, xcd_tile(blockIdx.x, n));
-  if constexpr (kMode == 0)
-    integrate_tile<V, KC, kExact>(items[wi.item].integ, work_tile(wi), smem);
-  else
-    integrate_tile<V, KC, kExact, true, kMode == 2 ? 1 : 0>(items[wi.item].integ, work_tile(wi),
-                                                             smem);
+  integrate_tile<kForm>((FuseArgs)(const IntegrateArgs *)&items[wi.item].integ, work_tile(wi), smem);
 }
 
-template <int C>
-static void launch_integ_class(const BatchPlan &P, const IntegGroup &g, hipStream_t s) {
-  // the LDS form exists for 8 and 4 bins per thread only (the host assigns
-  // no items to the other combinations)
-  if constexpr (mode_of_class(C) == 0 || vec_of_class(C) >= 4)
-    hipLaunchKernelGGL((batch_integrate_kernel<vec_of_class(C), views_of_class(C), exact_class(C),
-                                               mode_of_class(C)>),
-                       dim3(g.n), dim3(g.threads), g.shm, s, P.d_items, g.list, g.n);
-}
-
-template <int C>
-static void dispatch_integ_class(const BatchPlan &P, const IntegGroup &g, hipStream_t s) {
-  if constexpr (C < kIntegClasses) {
-    if (g.cls == C)
-      launch_integ_class<C>(P, g, s);
-    else
-      dispatch_integ_class<C + 1>(P, g, s);
+template <int kForm>
+static void launch_integ_form(const BatchPlan &P, const IntegGroup &g, hipStream_t s) {
+  if constexpr (kForm < kFuseForms) {
+    if (g.form != kForm) return launch_integ_form<kForm + 1>(P, g, s);
+    if constexpr (form_exists(kForm))
+      hipLaunchKernelGGL(batch_integrate_kernel<kForm>, dim3(g.n), dim3(64 * g.waves),
+                         FuseLds::bytes(g.waves), s, P.d_items, g.list, g.n);
   }
 }
 
@@ -229,7 +210,7 @@ int batch_record(BatchPlan &P, hipStream_t s, hipStream_t side, hipEvent_t fork,
     hipLaunchKernelGGL(batch_conf_kernel, dim3(P.n_conf), dim3(256), 0, s, P.d_items, P.d_conf,
                        P.n_conf);
   for (const IntegGroup &g : P.integ)
-    if (g.n) dispatch_integ_class<0>(P, g, s);
+    if (g.n) launch_integ_form<0>(P, g, s);
   if (branch)
     if (int rc = check_hip(hipStreamWaitEvent(s, join, 0), "batch join")) return rc;
   return check_hip(hipGetLastError(), "batch phases");

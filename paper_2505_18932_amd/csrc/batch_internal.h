@@ -4,54 +4,13 @@
 #include <vector>
 
 #include "splat_device.h"
-#include "tsdf_device.h"
+#include "fuse_device.h"
 
 namespace gg {
 
-constexpr int kConfTileFloats = kConfLH * kConfLW;
-
-// Fusion work is split into classes that each run one specialisation of the
-// plain kernel's device function: bins per thread (8, 4, 2, 1) times view
-// count (1, 2, 3, 4, 6, 8 compile-time, other counts at run time, or every
-// sample by IEEE division) times the volume stream's form (direct with the
-// carry decided at run time; through LDS without or with a carry, for 8 or
-// 4 bins per thread).
-constexpr int kVecClasses = 4, kViewClasses = 8, kModeClasses = 3;
-constexpr int kIntegClasses = kVecClasses * kViewClasses * kModeClasses;
 constexpr int kLightCounters = 2;  // persistent phases: bin count, bin fill
 constexpr int kXcds = 8;           // each phase keeps one counter per XCD
 constexpr int kBatchCounters = kLightCounters * kXcds;
-
-__host__ __device__ constexpr int vec_of_class(int c) {
-  return 8 >> ((c / kModeClasses) / kViewClasses);
-}
-__host__ __device__ constexpr int views_of_class(int c) {
-  return ((c / kModeClasses) % kViewClasses) < 4
-             ? ((c / kModeClasses) % kViewClasses) + 1
-             : (((c / kModeClasses) % kViewClasses) == 4
-                    ? 6
-                    : (((c / kModeClasses) % kViewClasses) == 5 ? 8 : 0));
-}
-__host__ __device__ constexpr bool exact_class(int c) {
-  return (c / kModeClasses) % kViewClasses == 7;
-}
-// 0: direct volume stream, carry at run time; 1: through LDS, no carry; 2:
-// through LDS, carried
-__host__ __device__ constexpr int mode_of_class(int c) { return c % kModeClasses; }
-
-inline int integ_class(int V, int K, bool exact_only, int mode) {
-  const int vi = V == 8 ? 0 : (V == 4 ? 1 : (V == 2 ? 2 : 3));
-  int kc = 6;  // runtime view count
-  if (exact_only)
-    kc = 7;
-  else if (K >= 1 && K <= 4)
-    kc = K - 1;
-  else if (K == 6)
-    kc = 4;
-  else if (K == 8)
-    kc = 5;
-  return (vi * kViewClasses + kc) * kModeClasses + mode;
-}
 
 // Everything one item's phases need, in device memory (read with scalar
 // loads: the descriptor address is uniform per work entry).
@@ -93,12 +52,10 @@ __device__ __forceinline__ uint32_t work_tile(const WorkItem &w) {
   return (uint32_t)w.x | ((uint32_t)w.y << 16);
 }
 
-// One fusion launch of the batch: the tiles of every item in one
-// specialisation (class) and workgroup size.
+// One fusion launch of the batch: the tiles of every item of one form and
+// workgroup size.
 struct IntegGroup {
-  int cls = 0;
-  uint32_t threads = 0;
-  size_t shm = 0;              // dynamic LDS (its items' largest)
+  int form = 0, waves = 0;
   WorkItem *list = nullptr;    // device
   uint32_t n = 0;
 };

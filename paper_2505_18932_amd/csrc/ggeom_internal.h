@@ -187,9 +187,20 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t wg, uint32_t n) {
 // ---------------------------------------------------------------------------
 // fusion (tsdf.hip)
 
+// Cells of the depth ranges (cell_range): kCell x kCell source pixels.
+constexpr int kCell = 32;
+__host__ __device__ constexpr uint32_t cells_across(int32_t n) {
+  return (uint32_t)(n + kCell - 1) / (uint32_t)kCell;
+}
+
 struct ConfArgs {
   const float *depth;  // K x Hs x Ws
   float2 *table;       // K x Hs x (Ws + 1): (usable depth or +inf, omega), rows closed by (0, 0)
+  // 2 x ncells or null, ncells = K x cells_across(Hs) x cells_across(Ws): per cell the largest,
+  // then the least usable depth of the 3 x 3 cells from it (to the right and below), as float
+  // bits; set to 0 and +inf beforehand
+  uint32_t *cells;
+  uint32_t ncells;
   int32_t Ws, Hs, K;
   int32_t radius;      // (w - 1) / 2
   float tw2;           // conf_tau^2
@@ -197,10 +208,16 @@ struct ConfArgs {
   float scale;         // conf_scale
 };
 
+// The fusion's workgroup tile: consecutive target pixels.
+constexpr uint32_t kFusePix = 64;
+
 struct IntegrateArgs {
   Proj views[GG_MAX_VIEWS];  // target -> view k
+  float slack[GG_MAX_VIEWS][3];  // rounding bounds of the views' coordinates (find_live)
   const float2 *table;       // K x Hs x (Ws + 1) view table (table_pitch)
-  const float2 *bins;        // D x (z_d, tau_d)
+  const float2 *bins;        // D x (z_d, tau_d), the last repeated to a multiple of 8
+  const float *cells;        // ConfArgs::cells or null
+  uint32_t ncells;
   const float *mask;         // Ht x Wt or null
   const float *F_prev;       // may alias F
   const float *W_prev;
@@ -210,19 +227,15 @@ struct IntegrateArgs {
   int32_t *out_bin;
   int32_t K, Ws, Hs, D;
   uint32_t npix;     // Ht * Wt
-  uint32_t ns;       // Hs * Ws
   FastDiv wt_div;    // by Wt
-  FastDiv cpp_div;   // by chunks per pixel (D / V)
-  uint32_t cpp, ppb; // chunks per pixel, pixels per workgroup
-  uint32_t pw_shift; // 2^pw_shift neighbouring pixels share each wavefront row
   uint32_t nblocks;
   // tile order: band_T tiles per target row, visited in vertical bands of
   // band_B tiles across and band_H rows (band_T = 0: row-major)
   uint32_t band_T, band_B, band_H;
   float decay, cap;
-  int32_t carry;
   int32_t exact_only;  // 1: every sample takes IEEE division (extreme depths)
-  int32_t rows;        // 1: the launch reads the view tables with structured loads
+  int32_t test;        // 1: find_live applies
+  float zfar;          // above every bin depth
 };
 
 struct ExtractArgs {
@@ -303,9 +316,12 @@ struct BlendArgs {
 int launch_network_inputs(const NetArgs &a, hipStream_t s);
 int launch_blend(const BlendArgs &a, hipStream_t s);
 
-int launch_bins(const gg_tsdf_params &p, float2 *bins, hipStream_t s);
+int launch_bins(const gg_tsdf_params &p, float2 *bins, uint32_t *cells, uint32_t ncells,
+                hipStream_t s);
 int launch_conf(const ConfArgs &a, hipStream_t s);
-int launch_integrate(const IntegrateArgs &a, int V, uint32_t threads, hipStream_t s);
+int launch_integrate(const IntegrateArgs &a, hipStream_t s);
+// Which form of the fusion kernel a launch takes (bits of its template arguments).
+int integrate_form(const IntegrateArgs &a);
 int launch_extract(const ExtractArgs &a, int V, uint32_t threads, hipStream_t s);
 int launch_extract_backward(const ExtractArgs &a, hipStream_t s);
 int launch_tsdf_backward(const TsdfBackArgs &a, hipStream_t s);

@@ -9,28 +9,29 @@
 // multiply-adds are explicit fmaf; divide and square root are correctly
 // rounded) so that the volume and the extracted bins are bitwise
 // reproducible and equal to the plain definition.
-#include "tsdf_device.h"
+#include "fuse_device.h"
 
 namespace gg {
 
 // ---------------------------------------------------------------------------
 // depth bins: z_d = 1 / (1/z_near - d du), tau_d = trunc du z_d^2 (in bins)
 
+// (the last bin repeated to a multiple of kFuseBins, so that every chunk of
+// the fusion reads whole), and the start values of the cells' depth ranges.
+
 __global__ void bins_kernel(int32_t D, float z_near, float z_far, float trunc, int32_t in_bins,
-                            float2 *out) {
-  const int d = blockIdx.x * blockDim.x + threadIdx.x;
-  if (d >= D) return;
-  const float un = 1.0f / z_near;
-  const float uf = 1.0f / z_far;
-  const float du = (un - uf) / (float)(D - 1);
-  const float z = bin_depth(d, D, z_near, z_far);
-  out[d] = make_float2(z, in_bins ? (trunc * du) * (z * z) : trunc);
+                            float2 *out, uint32_t *cells, uint32_t ncells) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 2 * ncells) cells[i] = cell_start(i, ncells);
+  if (i < padded_bins(D)) out[i] = bin_record((int)i, D, z_near, z_far, trunc, in_bins);
 }
 
-int launch_bins(const gg_tsdf_params &p, float2 *bins, hipStream_t s) {
+int launch_bins(const gg_tsdf_params &p, float2 *bins, uint32_t *cells, uint32_t ncells,
+                hipStream_t s) {
   KernelTimer t("bins", s);
-  hipLaunchKernelGGL(bins_kernel, dim3((p.num_bins + 255) / 256), dim3(256), 0, s, p.num_bins,
-                     p.z_near, p.z_far, p.trunc, p.trunc_in_bins, bins);
+  const uint32_t n = 2 * ncells > padded_bins(p.num_bins) ? 2 * ncells : padded_bins(p.num_bins);
+  hipLaunchKernelGGL(bins_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p.num_bins,
+                     p.z_near, p.z_far, p.trunc, p.trunc_in_bins, bins, cells, ncells);
   return check_hip(hipGetLastError(), "bins_kernel");
 }
 
@@ -41,7 +42,7 @@ int launch_bins(const gg_tsdf_params &p, float2 *bins, hipStream_t s) {
 // drops it; omega), one 8-byte record per pixel, gathered by the fusion.
 
 __global__ __launch_bounds__(256) void conf_kernel(ConfArgs a) {
-  __shared__ float tile[kConfLH * kConfLW];
+  __shared__ float tile[kConfTileFloats];
   conf_tile(a, blockIdx.z, blockIdx.x, blockIdx.y, tile);
 }
 
@@ -52,82 +53,39 @@ int launch_conf(const ConfArgs &a, hipStream_t s) {
   return check_hip(hipGetLastError(), "conf_kernel");
 }
 
-template <int V, int KC, bool kExact, bool kStage, int kCarry, bool kRows = false>
-__global__ __launch_bounds__(1024) void integrate_kernel(IntegrateArgs a) {
-  extern __shared__ float smem[];
-  integrate_tile<V, KC, kExact, kStage, kCarry, kRows>(
-      a, band_tile(a, xcd_tile(blockIdx.x, a.nblocks)), smem);
+template <int kForm>
+__global__ __launch_bounds__(64 * kFuseMaxWaves) void integrate_kernel(IntegrateArgs args) {
+  extern __shared__ __align__(16) float smem[];
+  // the record is read in the argument segment (offset 0: the only argument)
+  const FuseArgs a = (FuseArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  integrate_tile<kForm>(a, band_tile(args, xcd_tile(blockIdx.x, args.nblocks)), smem);
 }
 
-template <int V, int KC, bool kStage, int kCarry>
-static void launch_integrate_vk(const IntegrateArgs &a, uint32_t threads, size_t shm,
-                                hipStream_t s) {
-  // structured view-table loads: only in the staged, carried forms with up to four views
-  // (the host sets a.rows where they pay; elsewhere the specialisation does not exist)
-  if constexpr (kStage && kCarry == 1 && KC >= 1 && KC <= 4) {
-    if (a.rows && !a.exact_only) {
-      hipLaunchKernelGGL((integrate_kernel<V, KC, false, kStage, kCarry, true>), dim3(a.nblocks),
-                         dim3(threads), shm, s, a);
-      return;
+// Structured view-table loads take three vector instructions per sample less
+// than range-checked raw ones; their resource's 14-bit stride holds rows of
+// at most 2047 records.
+int integrate_form(const IntegrateArgs &a) {
+  auto al = [](const void *p) { return ((uintptr_t)p & 15u) == 0; };
+  const bool vec = a.D % 4 == 0 && al(a.F) && al(a.W) && al(a.F_prev) && al(a.W_prev);
+  return (vec ? kFormVec : 0) | (vec && a.D % 32 == 0 ? kFormLines : 0) |
+         (table_rows_ok(a.Ws) ? kFormRows : 0) | (a.F_prev ? kFormCarry : 0);
+}
+
+template <int kForm>
+static void launch_form(const IntegrateArgs &a, int form, hipStream_t s) {
+  if constexpr (kForm < kFuseForms) {
+    if (form != kForm) return launch_form<kForm + 1>(a, form, s);
+    if constexpr (form_exists(kForm)) {
+      const int waves = fuse_waves(a.D, a.nblocks, form_direct(kForm));
+      hipLaunchKernelGGL(integrate_kernel<kForm>, dim3(a.nblocks), dim3(64 * waves),
+                         FuseLds::bytes(waves), s, a);
     }
   }
-  if (a.exact_only)
-    hipLaunchKernelGGL((integrate_kernel<V, KC, true, kStage, kCarry>), dim3(a.nblocks),
-                       dim3(threads), shm, s, a);
-  else
-    hipLaunchKernelGGL((integrate_kernel<V, KC, false, kStage, kCarry>), dim3(a.nblocks),
-                       dim3(threads), shm, s, a);
 }
 
-template <int V, bool kStage, int kCarry>
-static void launch_integrate_v(const IntegrateArgs &a, uint32_t threads, size_t shm,
-                               hipStream_t s) {
-  switch (a.K) {
-    case 1: launch_integrate_vk<V, 1, kStage, kCarry>(a, threads, shm, s); break;
-    case 2: launch_integrate_vk<V, 2, kStage, kCarry>(a, threads, shm, s); break;
-    case 3: launch_integrate_vk<V, 3, kStage, kCarry>(a, threads, shm, s); break;
-    case 4: launch_integrate_vk<V, 4, kStage, kCarry>(a, threads, shm, s); break;
-    case 6: launch_integrate_vk<V, 6, kStage, kCarry>(a, threads, shm, s); break;
-    case 8: launch_integrate_vk<V, 8, kStage, kCarry>(a, threads, shm, s); break;
-    default: launch_integrate_vk<V, 0, kStage, kCarry>(a, threads, shm, s); break;
-  }
-}
-
-template <int V>
-static void launch_integrate_staged(const IntegrateArgs &a, uint32_t threads, hipStream_t s) {
-  const size_t shm = integrate_lds_bytes<V>(threads, a.ppb, a.D, true);
-  if (a.carry)
-    launch_integrate_v<V, true, 1>(a, threads, shm, s);
-  else
-    launch_integrate_v<V, true, 0>(a, threads, shm, s);
-}
-
-// The volume stream goes through LDS (integrate_tile's kStage) where the
-// launch shape allows it: 4 or 8 bins per thread, 16 pixels per wavefront
-// row, whole groups of 4 chunks per wavefront, and the LDS within 64 KB.
-template <int V>
-static bool stage_fits(const IntegrateArgs &a, uint32_t threads) {
-  return a.pw_shift == 4 && a.cpp % 4 == 0 && threads % 64 == 0 &&
-         integrate_lds_bytes<V>(threads, a.ppb, a.D, true) <= 65536;
-}
-
-int launch_integrate(const IntegrateArgs &a, int V, uint32_t threads, hipStream_t s) {
+int launch_integrate(const IntegrateArgs &a, hipStream_t s) {
   KernelTimer t("integrate", s);
-  if (V == 8 && stage_fits<8>(a, threads))
-    launch_integrate_staged<8>(a, threads, s);
-  else if (V == 4 && stage_fits<4>(a, threads))
-    launch_integrate_staged<4>(a, threads, s);
-  else {
-    const size_t shm = integrate_lds_head(threads, a.ppb);
-    if (V == 8)
-      launch_integrate_v<8, false, -1>(a, threads, shm, s);
-    else if (V == 4)
-      launch_integrate_v<4, false, -1>(a, threads, shm, s);
-    else if (V == 2)
-      launch_integrate_v<2, false, -1>(a, threads, shm, s);
-    else
-      launch_integrate_v<1, false, -1>(a, threads, shm, s);
-  }
+  launch_form<0>(a, integrate_form(a), s);
   return check_hip(hipGetLastError(), "integrate_kernel");
 }
 
