@@ -757,6 +757,19 @@ static bool view_slack(const Proj &P, const gg_camera &tgt, float z_far, float *
   return true;
 }
 
+// True where every sample of the view has Z > 2^-40, in which the kernels' arithmetic keeps to
+// its fast form: Z is bilinear in the pixel and the depth, so its least is at a corner.
+static bool view_in_front(const Proj &P, const gg_camera &tgt, const gg_tsdf_params &prm,
+                          double slack) {
+  for (int c = 0; c < 8; ++c) {
+    const double z = (c & 4) ? prm.z_far * 1.01 : prm.z_near * 0.99;
+    const double h2 = (double)P.H[6] * ((c & 1) ? tgt.width : 0) +
+                      (double)P.H[7] * ((c & 2) ? tgt.height : 0) + (double)P.H[8];
+    if (!(z * h2 + (double)P.c[2] - slack > std::ldexp(1.0, -40))) return false;
+  }
+  return true;
+}
+
 // cells: the cells' depth ranges built with the table, or null.
 static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t K,
                                 const gg_camera &tgt, const gg_tsdf_params &prm, uint32_t band_px,
@@ -786,10 +799,15 @@ static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t 
   a.decay = prm.decay;
   a.cap = prm.weight_cap;
   a.exact_only = fast_reciprocal_safe(a.views, K, tgt, prm.z_far) ? 0 : 1;
-  a.test = K > 0 && !a.exact_only;
+  // The bounds below need bin depths between 0.99 z_near and 1.01 z_far: a bin's 1 / z is
+  // rounded by some 2^-22 / z_near, here less than 2^-9 / z_far.
+  a.test = K > 0 && !a.exact_only && prm.z_far < 8192.0f * prm.z_near;
   a.zfar = prm.z_far * 1.01f;
   for (int k = 0; k < K && a.test; ++k)
     a.test = view_slack(a.views[k], tgt, prm.z_far, a.slack[k]) ? 1 : 0;
+  a.front = a.test;
+  for (int k = 0; k < K && a.front; ++k)
+    a.front = view_in_front(a.views[k], tgt, prm, a.slack[k][2]) ? 1 : 0;
 }
 
 // The cells' place in a workspace of ws_bytes (null if it ends before them).

@@ -39,6 +39,16 @@ __host__ __device__ inline int fuse_waves(int D, uint32_t nblocks, bool direct) 
   return w;
 }
 
+// Whether a launch looks for views to drop (find_live) where it may: with one
+// or two views there is too little to drop, and in small launches, a round or
+// so of workgroups, the test's chain of loads is not hidden (measured, with
+// and without: 1280 x 720 K=1 D=128 207 and 185 us, 640 x 400 K=2 D=64 43 and
+// 40, 420 x 260 K=3 D=48 26.9 and 25.1; 512 x 288 K=4 D=96 50 and 53).  It may
+// not be left out where a sample can be behind its camera.
+__host__ __device__ inline bool fuse_tests(int K, uint32_t nblocks, bool front) {
+  return !front || (K > 2 && nblocks > 1536);
+}
+
 // LDS of a workgroup, in floats: F and W of the slab, F of each chunk's last
 // bin by slab parity, and the first crossings (64-bit).
 struct FuseLds {
@@ -325,9 +335,11 @@ __device__ __forceinline__ void find_live(FuseArgs a, const TileRect &rect, int 
     const uint32_t cell =
         (k * cells_across(a->Hs) + (uint32_t)ay) * cells_across(a->Ws) + (uint32_t)ax;
     const float far = gmem(a->cells)[cell], near = gmem(a->cells)[a->ncells + cell];
-    const bool fits = a1 - a0 < 6 && c1 - c0 < 6;
-    dead = dead || (fits && quad_max(far) - Zlo < -b1.y);
-    free = fits && quad_min(near) - Zhi > b1.y;
+    // no branch: a load that only one side waits for would have every slab's
+    // first view wait for all memory traffic before it, the stores too
+    const bool fits = (a1 - a0 < 6) & (c1 - c0 < 6);
+    dead |= fits & (quad_max(far) - Zlo < -b1.y);
+    free = fits & (quad_min(near) - Zhi > b1.y);
   }
   // far enough from the camera plane for the bounds above
   const bool clear = Zlo > 0x1p-40f;
@@ -493,9 +505,10 @@ struct SlabDirect {
   }
 };
 
-// The crossing between bins d and d + 1: the bin above, the interpolated depth below.
-__device__ __forceinline__ unsigned long long crossing_key(FuseArgs a, int d, float f0, float f1) {
-  const float za = gload2(a->bins + d).x, zb = gload2(a->bins + d + 1).x;
+// The crossing between bins d and d + 1, of depths za and zb: the bin above,
+// the interpolated depth below.
+__device__ __forceinline__ unsigned long long crossing_key(int d, float za, float zb, float f0,
+                                                           float f1) {
   const float frac = f0 / (f0 - f1);
   return ((unsigned long long)(uint32_t)d << 32) | __float_as_uint(za + (zb - za) * frac);
 }
@@ -551,6 +564,8 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
     for (int v = 0; v < kFuseBins; ++v) S[v] = Wo[v] = 0.0f;
     const uint32_t sub = (uint32_t)slab & (lv.slabs() - 1u);
     if (a->test && sub == 0) find_live(a, rect, slab * waves + wave, waves, lv);
+    // without a view and a volume to carry, the chunk is zero and has no crossing
+    bool some = kCarry;
     if (d0 < D) {
       Chunk b;  // bins past D repeat the last one
       const GG_CONSTANT float *bt = (const GG_CONSTANT float *)(const float *)(a->bins + d0);
@@ -560,12 +575,13 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
         b.tau[v] = bt[2 * v + 1];
       }
       uint64_t live = a->K ? 0x1111111111111111ull >> (64 - 4 * a->K) : 0ull, free = 0;
-      bool front = false;
+      bool front = a->front != 0;
       if (a->test) {
         live = lv.of(lv.live, sub, a->K);
         free = lv.of(lv.free, sub, a->K);
         front = (lv.of(lv.behind, sub, a->K) & live) == 0;
       }
+      some = some || live != 0;
 #pragma nounroll
       while (live) {
         const int bit = __builtin_ctzll(live), k = __builtin_amdgcn_readfirstlane(bit >> 2);
@@ -589,25 +605,37 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
     __syncthreads();  // the slab's previous F and W are in LDS; the last slab is stored
     const float decay = a->decay, cap = a->cap;
     float Fn[kFuseBins], Wn[kFuseBins];
+    if (some) {
 #pragma unroll
-    for (int q = 0; q < kFuseBins / 4; ++q) {
-      gg_v4f f = {0.0f, 0.0f, 0.0f, 0.0f}, w = f;
-      const uint32_t at = slabs.quad(lane, wave, q);
-      if constexpr (kCarry) {
-        f = *(const gg_v4f *)(L.vol[0] + at);
-        w = *(const gg_v4f *)(L.vol[1] + at);
-      }
+      for (int q = 0; q < kFuseBins / 4; ++q) {
+        gg_v4f f = {0.0f, 0.0f, 0.0f, 0.0f}, w = f;
+        const uint32_t at = slabs.quad(lane, wave, q);
+        if constexpr (kCarry) {
+          f = *(const gg_v4f *)(L.vol[0] + at);
+          w = *(const gg_v4f *)(L.vol[1] + at);
+        }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int v = 4 * q + i;
-        const float wp = kCarry ? fminf((decay * w[i]) * m, cap) : 0.0f;
-        const float wn = wp + Wo[v];
-        Fn[v] = wn > 0.0f ? fmaf(wp, f[i], S[v]) / wn : 0.0f;
-        Wn[v] = wn;
+        for (int i = 0; i < 4; ++i) {
+          const int v = 4 * q + i;
+          const float wp = kCarry ? fminf((decay * w[i]) * m, cap) : 0.0f;
+          const float wn = wp + Wo[v];
+          float mean = fmaf(wp, f[i], S[v]) / wn;
+          asm volatile("" : "+v"(mean));  // no branch around each division: four run abreast
+          Fn[v] = wn > 0.0f ? mean : 0.0f;
+          Wn[v] = wn;
+        }
+        *(gg_v4f *)(L.vol[0] + at) = (gg_v4f){Fn[4 * q], Fn[4 * q + 1], Fn[4 * q + 2], Fn[4 * q + 3]};
+        *(gg_v4f *)(L.vol[1] + at) = (gg_v4f){Wn[4 * q], Wn[4 * q + 1], Wn[4 * q + 2], Wn[4 * q + 3]};
+        schedule_fence();
       }
-      *(gg_v4f *)(L.vol[0] + at) = (gg_v4f){Fn[4 * q], Fn[4 * q + 1], Fn[4 * q + 2], Fn[4 * q + 3]};
-      *(gg_v4f *)(L.vol[1] + at) = (gg_v4f){Wn[4 * q], Wn[4 * q + 1], Wn[4 * q + 2], Wn[4 * q + 3]};
-      schedule_fence();
+    } else {
+#pragma unroll
+      for (int v = 0; v < kFuseBins; ++v) Fn[v] = Wn[v] = 0.0f;
+#pragma unroll
+      for (int q = 0; q < kFuseBins / 4; ++q) {
+        const uint32_t at = slabs.quad(lane, wave, q);
+        *(gg_v4f *)(L.vol[0] + at) = *(gg_v4f *)(L.vol[1] + at) = (gg_v4f){0.0f, 0.0f, 0.0f, 0.0f};
+      }
     }
     // F of the last bin of the chunk before: the other wavefronts' after the
     // barrier, the previous slab's (kept by parity) before it
@@ -625,7 +653,7 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
         load_volume(s0 + step);
       }
     }
-    if (a->out_depth && d0 < D) {
+    if (a->out_depth && some && d0 < D) {
       // F > 0 means an observed bin (an unobserved one holds 0)
       if (wave > 0) Fprev = edge[(par * waves + wave - 1) * (int)kFusePix];
       uint64_t hit = 0;
@@ -639,9 +667,11 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
       }
       if (hit) {
         // the chunk's first crossing (the first bin of all has Fprev = 0); the
-        // smallest bin of the pixel wins (order-free)
+        // smallest bin of the pixel wins (order-free).  The depths by scalar
+        // loads: a vector load's wait would include the stores above.
+        const GG_CONSTANT float *bt = (const GG_CONSTANT float *)(const float *)(a->bins + d0);
         int d = -1;
-        float f0 = 1.0f, f1 = 0.0f;
+        float f0 = 1.0f, f1 = 0.0f, za = 0.0f, zb = 0.0f;
 #pragma unroll
         for (int v = kFuseBins - 1; v >= 0; --v) {
           const float g0 = v ? Fn[v ? v - 1 : 0] : Fprev;
@@ -649,9 +679,11 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
             d = d0 + v - 1;
             f0 = g0;
             f1 = Fn[v];
+            za = v ? bt[2 * v - 2] : bt[d0 ? -2 : 0];
+            zb = bt[2 * v];
           }
         }
-        if (d >= 0) atomicMin(&L.best[lane], crossing_key(a, d, f0, f1));
+        if (d >= 0) atomicMin(&L.best[lane], crossing_key(d, za, zb, f0, f1));
       }
     }
   }

@@ -235,6 +235,7 @@ struct IntegrateArgs {
   float decay, cap;
   int32_t exact_only;  // 1: every sample takes IEEE division (extreme depths)
   int32_t test;        // 1: find_live applies
+  int32_t front;       // 1: every sample of every view is in front of its camera
   float zfar;          // above every bin depth
 };
 

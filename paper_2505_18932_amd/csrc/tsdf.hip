@@ -85,7 +85,9 @@ static void launch_form(const IntegrateArgs &a, int form, hipStream_t s) {
 
 int launch_integrate(const IntegrateArgs &a, hipStream_t s) {
   KernelTimer t("integrate", s);
-  launch_form<0>(a, integrate_form(a), s);
+  IntegrateArgs b = a;
+  b.test = a.test && fuse_tests(a.K, a.nblocks, a.front != 0);
+  launch_form<0>(b, integrate_form(b), s);
   return check_hip(hipGetLastError(), "integrate_kernel");
 }
 
