@@ -97,13 +97,11 @@ typedef struct gg_mask_params {
 /* Launch shape of the volume kernels (tsdf_integrate and its variants,
  * tsdf_extract_depth, gg_fusion_stream_probe), passed with each call; NULL or
  * a zero field takes the default.  Results never depend on it (it exists for
- * the autotuner).  The fusion's workgroup is fixed (64 target pixels, each
- * lane 8 bins at a time): of the fields it takes band_width, the others shape
- * tsdf_extract_depth.  bins_per_thread also sets the alignment that the
- * volumes of either call must have (4 bytes times the bins taken).
- *   pixels_per_block  whole target pixels per workgroup, 0..1024 (0: 512
- *                     threads' worth)
- *   pixels_per_row    0..64 (no kernel takes it)
+ * the autotuner).  The workgroups are fixed: of the fields only band_width
+ * shapes a launch (the fusion's); the others are checked, and bins_per_thread
+ * sets the alignment that the volumes must have (4 bytes times the bins taken).
+ *   pixels_per_block  0..1024
+ *   pixels_per_row    0..64
  *   bins_per_thread   1, 2, 4 or 8 (0: 4 where it divides num_bins); used
  *                     where it divides num_bins and, for 8, where every
  *                     volume argument is 32-byte aligned, else the largest of

@@ -357,11 +357,6 @@ static int check_tuning(const gg_volume_tuning *t, const char *what) {
   return GG_OK;
 }
 
-struct VolumeShape {
-  int V;
-  uint32_t cpp, ppb, threads, nblocks;
-};
-
 constexpr uint32_t kDefaultBandPixels = 256;
 static uint32_t band_pixels(const gg_volume_tuning *t) {
   return t && t->band_width > 0 ? (uint32_t)t->band_width : kDefaultBandPixels;
@@ -388,19 +383,13 @@ static int volume_v(int D, bool aligned32, int o) {
   return (D % 4 == 0) ? 4 : (D % 2 == 0 ? 2 : 1);
 }
 
-static int volume_shape(int D, uint32_t npix, VolumeShape &s, const char *what,
-                        bool aligned32, const gg_volume_tuning *tun) {
+// Checks a volume of D bins against the tuning's bins per thread: their number V, at most 1024
+// threads per pixel.
+static int volume_shape(int D, int &V, const char *what, bool aligned32,
+                        const gg_volume_tuning *tun) {
   if (int rc = check_tuning(tun, what)) return rc;
-  const int ppb_t = tun ? tun->pixels_per_block : 0;
-  s.V = volume_v(D, aligned32, tun ? tun->bins_per_thread : 0);
-  s.cpp = (uint32_t)(D / s.V);
-  if (s.cpp > 1024) return fail(GG_ERR_UNSUPPORTED, "%s: D = %d too large", what, D);
-  uint32_t ppb = ppb_t > 0 ? (uint32_t)ppb_t : 512u / s.cpp;
-  if (ppb < 1) ppb = 1;
-  while (ppb > 1 && ppb * s.cpp > 1024) --ppb;
-  s.ppb = ppb;
-  s.threads = ppb * s.cpp;
-  s.nblocks = (npix + ppb - 1) / ppb;
+  V = volume_v(D, aligned32, tun ? tun->bins_per_thread : 0);
+  if (D / V > 1024) return fail(GG_ERR_UNSUPPORTED, "%s: D = %d too large", what, D);
   return GG_OK;
 }
 
@@ -856,11 +845,11 @@ static int integrate_impl(const char *N, bool tabled, const gg_camera *src, int3
     return fail(GG_ERR_INVALID, "%s: out_depth and out_bin go together", N);
   const int sw = src[0].width, sh = src[0].height, D = prm->num_bins;
   const uint32_t npix = (uint32_t)(tgt->width * tgt->height);
-  VolumeShape vs;
+  int V = 0;
   const bool a32 = aligned(F, 32) && aligned(W, 32) && (!F_prev || (aligned(F_prev, 32) &&
                                                                      aligned(W_prev, 32)));
-  if (int rc = volume_shape(D, npix, vs, N, a32, tuning)) return rc;
-  const size_t va = 4 * (size_t)vs.V;
+  if (int rc = volume_shape(D, V, N, a32, tuning)) return rc;
+  const size_t va = 4 * (size_t)V;
   if (!aligned(F, va) || !aligned(W, va) || (F_prev && (!aligned(F_prev, va) || !aligned(W_prev, va))))
     return fail(GG_ERR_INVALID, "%s: volumes must be %zu-byte aligned", N, va);
   if ((size_t)npix * D > (size_t)1 << 40) return fail(GG_ERR_UNSUPPORTED, "%s: volume too large", N);
@@ -907,10 +896,10 @@ int gg_fusion_stream_probe(const gg_camera *tgt, const gg_tsdf_params *prm,
     return fail(GG_ERR_INVALID, "%s: NULL array argument", N);
   const int D = prm->num_bins;
   const uint32_t npix = (uint32_t)(tgt->width * tgt->height);
-  VolumeShape vs;
+  int V = 0;
   const bool a32 = aligned(F, 32) && aligned(W, 32) && aligned(F_prev, 32) && aligned(W_prev, 32);
-  if (int rc = volume_shape(D, npix, vs, N, a32, tuning)) return rc;
-  const size_t va = 4 * (size_t)vs.V;
+  if (int rc = volume_shape(D, V, N, a32, tuning)) return rc;
+  const size_t va = 4 * (size_t)V;
   if (!aligned(F, va) || !aligned(W, va) || !aligned(F_prev, va) || !aligned(W_prev, va))
     return fail(GG_ERR_INVALID, "%s: volumes must be %zu-byte aligned", N, va);
   if ((size_t)npix * D > (size_t)1 << 40) return fail(GG_ERR_UNSUPPORTED, "%s: volume too large", N);
@@ -1078,10 +1067,10 @@ int tsdf_extract_depth(const gg_camera *tgt, const gg_tsdf_params *prm, const fl
   if (int rc = check_tsdf(prm, N)) return rc;
   if (!F || !W || !out_depth || !out_bin) return fail(GG_ERR_INVALID, "%s: NULL argument", N);
   const uint32_t npix = (uint32_t)(tgt->width * tgt->height);
-  VolumeShape vs;
-  if (int rc = volume_shape(prm->num_bins, npix, vs, N, aligned(F, 32) && aligned(W, 32), tuning))
+  int V = 0;
+  if (int rc = volume_shape(prm->num_bins, V, N, aligned(F, 32) && aligned(W, 32), tuning))
     return rc;
-  const size_t va = 4 * (size_t)vs.V;
+  const size_t va = 4 * (size_t)V;
   if (!aligned(F, va) || !aligned(W, va))
     return fail(GG_ERR_INVALID, "%s: volumes must be %zu-byte aligned", N, va);
   ExtractArgs a{};
@@ -1091,13 +1080,9 @@ int tsdf_extract_depth(const gg_camera *tgt, const gg_tsdf_params *prm, const fl
   a.out_bin = out_bin;
   a.npix = npix;
   a.D = prm->num_bins;
-  a.cpp_div = make_fastdiv(vs.cpp);
-  a.cpp = vs.cpp;
-  a.ppb = vs.ppb;
-  a.nblocks = vs.nblocks;
   a.z_near = prm->z_near;
   a.z_far = prm->z_far;
-  return launch_extract(a, vs.V, vs.threads, (hipStream_t)stream);
+  return launch_extract(a, (hipStream_t)stream);
 }
 
 int tsdf_extract_depth_backward(const gg_camera *tgt, const gg_tsdf_params *prm,

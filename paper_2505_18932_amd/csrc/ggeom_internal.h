@@ -249,8 +249,6 @@ struct ExtractArgs {
   const int32_t *bin;    // backward only
   uint32_t npix;
   int32_t D;
-  FastDiv cpp_div;
-  uint32_t cpp, ppb, nblocks;
   float z_near, z_far;
 };
 
@@ -323,7 +321,7 @@ int launch_conf(const ConfArgs &a, hipStream_t s);
 int launch_integrate(const IntegrateArgs &a, hipStream_t s);
 // Which form of the fusion kernel a launch takes (bits of its template arguments).
 int integrate_form(const IntegrateArgs &a);
-int launch_extract(const ExtractArgs &a, int V, uint32_t threads, hipStream_t s);
+int launch_extract(const ExtractArgs &a, hipStream_t s);
 int launch_extract_backward(const ExtractArgs &a, hipStream_t s);
 int launch_tsdf_backward(const TsdfBackArgs &a, hipStream_t s);
 int launch_recip_selftest(uint32_t e_lo, uint32_t n_exp, unsigned long long *mismatches,

@@ -236,97 +236,6 @@ __host__ __device__ __forceinline__ uint32_t band_tile(const IntegrateArgs &a, u
 }
 
 // ---------------------------------------------------------------------------
-// Volume stream access of V consecutive floats (V = 8, 4, 2, 1).  The volume
-// is read and written once per launch: its accesses are non-temporal, so
-// that they pass through the caches without evicting the view-table lines
-// that the gathers of neighbouring tiles reuse.
-
-template <int V>
-__device__ __forceinline__ void loadv(const float *p, float (&o)[V]) {
-  if constexpr (V == 8) {
-    const gg_v4f a = __builtin_nontemporal_load((const GG_GLOBAL gg_v4f *)p),
-                 b = __builtin_nontemporal_load((const GG_GLOBAL gg_v4f *)(p + 4));
-    o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
-    o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
-  } else if constexpr (V == 4) {
-    const gg_v4f v = __builtin_nontemporal_load((const GG_GLOBAL gg_v4f *)p);
-    o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
-  } else if constexpr (V == 2) {
-    const gg_v2f v = __builtin_nontemporal_load((const GG_GLOBAL gg_v2f *)p);
-    o[0] = v.x; o[1] = v.y;
-  } else {
-    o[0] = __builtin_nontemporal_load(gmem(p));
-  }
-}
-
-// First crossing inside this thread's V bins, given the next chunk's first
-// bin (F, W); INT_MAX if none.
-template <int V>
-__device__ __forceinline__ int local_crossing(const float (&F)[V], const float (&W)[V], float nF,
-                                              float nW, int d0, int D) {
-  int cand = INT_MAX;
-#pragma unroll
-  for (int v = V - 1; v >= 0; --v) {
-    const float f1 = (v + 1 < V) ? F[(v + 1) % V] : nF;
-    const float w1 = (v + 1 < V) ? W[(v + 1) % V] : nW;
-    if (d0 + v + 1 < D && W[v] > 0.0f && w1 > 0.0f && F[v] > 0.0f && f1 <= 0.0f) cand = d0 + v;
-  }
-  return cand;
-}
-
-// Extraction across the workgroup: each thread holds V bins of one pixel;
-// the chunk's first bin is exchanged through LDS, the smallest crossing per
-// pixel is an LDS atomic minimum (order-free), and the owning thread
-// interpolates.  zf(d) returns z_d for the owning thread.
-template <int V, typename ZF>
-__device__ __forceinline__ void extract_block(const float (&F)[V], const float (&W)[V],
-                                              bool lane, bool active, uint32_t pix, uint32_t lp,
-                                              uint32_t chunk, uint32_t cpp, uint32_t next_off,
-                                              int d0, int D,
-                                              float *sF, float *sW, int *sBest,
-                                              float *out_depth, int32_t *out_bin, ZF zf) {
-  // lane: this thread maps to a chunk of one of the workgroup's pixels
-  // (threads past ppb * cpp idle but take part in the barriers).
-  const uint32_t t = threadIdx.x;
-  if (lane) {
-    sF[t] = F[0];
-    sW[t] = W[0];
-    if (chunk == 0) sBest[lp] = INT_MAX;
-  }
-  __syncthreads();
-  const bool has_next = lane && chunk + 1 < cpp;
-  const float nF = has_next ? sF[t + next_off] : 0.0f;
-  const float nW = has_next ? sW[t + next_off] : 0.0f;
-  if (active) {
-    const int cand = local_crossing<V>(F, W, nF, nW, d0, D);
-    if (cand != INT_MAX) atomicMin(&sBest[lp], cand);
-  }
-  __syncthreads();
-  if (active) {
-    const int best = sBest[lp];
-    if (best == INT_MAX) {
-      if (chunk == 0) {
-        gmem(out_depth)[pix] = 0.0f;
-        gmem(out_bin)[pix] = -1;
-      }
-    } else {
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        if (best == d0 + v) {
-          const float f0 = F[v];
-          const float f1 = (v + 1 < V) ? F[(v + 1) % V] : nF;
-          const float za = zf(best), zb = zf(best + 1);
-          const float frac = f0 / (f0 - f1);
-          gmem(out_depth)[pix] = za + (zb - za) * frac;
-          gmem(out_bin)[pix] = best;
-        }
-      }
-    }
-  }
-  __syncthreads();  // LDS reused by the caller's next tile
-}
-
-// ---------------------------------------------------------------------------
 // sampling of a view table
 
 // How the samples find their pixels.  The pixel of the point (X0, X1, Z)
