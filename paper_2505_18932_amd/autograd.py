@@ -25,6 +25,7 @@ class SplatFn(torch.autograd.Function):
         ctx.save_for_backward(depth, rgb_u8, out["win_idx"], out["depth"], out["rgb"], out["tape"])
         ctx.cams = (ops.cameras(src), ops.camera(tgt), ops.splat_params(params))
         ctx.mark_non_differentiable(out["win_idx"])
+        ctx.set_materialize_grads(False)  # no zero gradients of the size of win_idx
         return out["rgb"], out["depth"], out["alpha"], out["win_idx"]
 
     @staticmethod
@@ -33,11 +34,11 @@ class SplatFn(torch.autograd.Function):
         src, tgt, params = ctx.cams
         fwd = dict(win_idx=win, depth=od, rgb=orgb, tape=tape)
 
-        def c(t):
-            return None if t is None else t.contiguous()
+        def c(t, out):
+            return torch.zeros_like(out) if t is None else t.contiguous()
 
         gd, gc = ops.splat_views_backward(src, depth.detach(), rgb_u8, tgt, params, fwd,
-                                          c(g_rgb), c(g_depth), c(g_alpha))
+                                          c(g_rgb, orgb), c(g_depth, od), c(g_alpha, od))
         return gd, gc, None, None, None, None
 
 
@@ -53,6 +54,9 @@ class TsdfFn(torch.autograd.Function):
         ctx.save_for_backward(depth, F, W, b)
         ctx.cams = (ops.cameras(src), ops.camera(tgt), ops.tsdf_params(params))
         ctx.mark_non_differentiable(b, F, W)
+        # autograd would fill zero gradients of F, W and bin for backward: at 1920 x 1080, D = 256
+        # twice 2.1 GB, 607 us of a training step's 6.3 ms
+        ctx.set_materialize_grads(False)
         return dep, b, F, W
 
     @staticmethod
@@ -60,7 +64,7 @@ class TsdfFn(torch.autograd.Function):
         depth, F, W, b = ctx.saved_tensors
         src, tgt, params = ctx.cams
         if g_dep is None:
-            return (None,) * 9
+            g_dep = torch.zeros(b.shape, dtype=F.dtype, device=F.device)
         g2 = ops.tsdf_extract_depth_backward(tgt, params, F, W, b, g_dep.contiguous())
         gd = ops.tsdf_integrate_backward(src, depth.detach(), tgt, params, F, W, b, g2)
         return gd, None, None, None, None, None, None, None, None
