@@ -806,13 +806,16 @@ static uint32_t *cells_of(const TsdfLayout &L, char *w, size_t ws_bytes) {
 
 // The view table (per source pixel: usable depth, fusion weight) and the
 // bin depths into the workspace: the part of the fusion that depends on the
-// depth maps only.
+// depth maps only.  ranges: the fusion's view test will read the cells' depth ranges (else they
+// are set to hold every depth, for a later call on the same table).
 static int build_view_table(const gg_camera *src, int32_t K, const float *depth,
                             const gg_tsdf_params *prm, const TsdfLayout &L, char *w,
-                            uint32_t *cells, hipStream_t s) {
+                            uint32_t *cells, bool ranges, hipStream_t s) {
   const int sw = src[0].width, sh = src[0].height;
-  if (int rc = launch_bins(*prm, (float2 *)(w + L.bins), cells, cells ? L.ncells : 0u, s)) return rc;
-  return launch_conf(conf_args(depth, (float2 *)(w + L.table), cells, sw, sh, K, prm), s);
+  if (int rc = launch_bins(*prm, (float2 *)(w + L.bins), cells, cells ? L.ncells : 0u, ranges, s))
+    return rc;
+  return launch_conf(conf_args(depth, (float2 *)(w + L.table), ranges ? cells : nullptr, sw, sh, K,
+                               prm), s);
 }
 
 int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
@@ -823,7 +826,7 @@ int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
   if (!depth) return fail(GG_ERR_INVALID, "%s: NULL array argument", N);
   const TsdfLayout L = tsdf_layout(K, src[0].width, src[0].height, prm->num_bins, false);
   if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
-  return build_view_table(src, K, depth, prm, L, (char *)ws, cells_of(L, (char *)ws, ws_bytes),
+  return build_view_table(src, K, depth, prm, L, (char *)ws, cells_of(L, (char *)ws, ws_bytes), true,
                           (hipStream_t)stream);
 }
 
@@ -860,11 +863,12 @@ static int integrate_impl(const char *N, bool tabled, const gg_camera *src, int3
   float2 *table = (float2 *)(w + L.table);
   float2 *bins = (float2 *)(w + L.bins);
   uint32_t *cells = cells_of(L, w, ws_bytes);
-  if (!tabled)
-    if (int rc = build_view_table(src, K, depth, prm, L, w, cells, s)) return rc;
   IntegrateArgs a{};
   make_integrate_args(a, src, K, *tgt, *prm, band_pixels(tuning), table, bins, (const float *)cells,
                       temporal_mask, F_prev, W_prev, F, W, out_depth, out_bin);
+  a.test = a.test && fuse_tests(K, a.nblocks, a.front != 0);
+  if (!tabled)
+    if (int rc = build_view_table(src, K, depth, prm, L, w, cells, a.test != 0, s)) return rc;
   return launch_integrate(a, s);
 }
 
@@ -907,7 +911,7 @@ int gg_fusion_stream_probe(const gg_camera *tgt, const gg_tsdf_params *prm,
   if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
   hipStream_t s = (hipStream_t)stream;
   float2 *bins = (float2 *)((char *)ws + L.bins);
-  if (int rc = launch_bins(*prm, bins, nullptr, 0, s)) return rc;
+  if (int rc = launch_bins(*prm, bins, nullptr, 0, false, s)) return rc;
   // the fusion kernel's own launch with no views: every voxel only decays
   // its carried weight (W = min(decay W_prev, cap), F = that weight times
   // F_prev over itself), so the kernel moves exactly its volume stream
@@ -1124,7 +1128,7 @@ int tsdf_integrate_backward(const gg_camera *src, int32_t K, const float *depth,
   char *w = (char *)ws;
   float2 *table = (float2 *)(w + L.table);
   float2 *bins = (float2 *)(w + L.bins);
-  if (int rc = launch_bins(*prm, bins, nullptr, 0, s)) return rc;
+  if (int rc = launch_bins(*prm, bins, nullptr, 0, false, s)) return rc;
   if (int rc = launch_conf(conf_args(depth, table, nullptr, sw, sh, K, prm), s)) return rc;
   TsdfBackArgs a{};
   fill_views(src, K, tgt, a.views);
@@ -1316,7 +1320,7 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
       count_words += (size_t)K * sl[i].ntiles + 1;
     }
     const uint32_t ctx = (uint32_t)((sw + kConfTX - 1) / kConfTX),
-                   cty = (uint32_t)((sh + kConfTY - 1) / kConfTY);
+                   cty = (uint32_t)((sh + kConfTY * kBatchConfRows - 1) / (kConfTY * kBatchConfRows));
     if (ctx > 65535 || cty > 65535) return fail(GG_ERR_UNSUPPORTED, "%s: image too large", N);
     for (int k = 0; k < K; ++k)
       for (uint32_t y = 0; y < cty; ++y)
@@ -1381,8 +1385,10 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
     uint32_t *cells = (uint32_t *)(dv + o_cells[i]);
     d.conf = conf_args(it.depth, table, cells, sw, sh, it.K, &it.tsdf);
     make_integrate_args(d.integ, it.src, it.K, it.tgt, it.tsdf, band_pixels(&it.volume), table,
-                        bins, (const float *)cells, it.temporal_mask, it.F_prev, it.W_prev, it.F, it.W, it.out_depth,
-                        it.out_bin);
+                        bins, (const float *)cells, it.temporal_mask, it.F_prev, it.W_prev, it.F,
+                        it.W, it.out_depth, it.out_bin);
+    // (the batch's tiles run together: no launch is small)
+    d.integ.test = d.integ.test && fuse_tests(it.K, UINT32_MAX, d.integ.front != 0);
     if (it.rgb) {
       make_splat_args(d.splat, it.src, it.K, it.depth, it.rgb, it.tgt, it.splat, sl[i],
                       dv + o_splat[i]);

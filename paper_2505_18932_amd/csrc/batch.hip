@@ -31,7 +31,7 @@ __global__ void batch_bins_kernel(const BatchItem *__restrict__ items) {
   for (uint32_t d = threadIdx.x; d < padded_bins(it.D); d += blockDim.x)
     gstore2(it.bins + d, bin_record((int)d, it.D, it.z_near, it.z_far, it.trunc, it.trunc_in_bins));
   for (uint32_t c = threadIdx.x; c < 2 * it.conf.ncells; c += blockDim.x)
-    gmem(it.conf.cells)[c] = cell_start(c, it.conf.ncells);
+    gmem(it.conf.cells)[c] = cell_start(c, it.conf.ncells, true);
 }
 
 // Dynamic work distribution in chunks, XCD-aware.  Entries differ in cost by
@@ -98,9 +98,9 @@ __device__ __forceinline__ void for_each_entry(uint32_t n, uint32_t chunk, uint3
 __global__ __launch_bounds__(256) void batch_conf_kernel(const BatchItem *__restrict__ items,
                                                          const WorkItem *__restrict__ work,
                                                          uint32_t n) {
-  __shared__ float tile[kConfTileFloats];
+  __shared__ float tile[conf_tile_floats(kBatchConfRows)];
   const WorkItem wi = uniform_entry(work, xcd_tile(blockIdx.x, n));
-  conf_tile(items[wi.item].conf, wi.k, wi.x, wi.y, tile);
+  conf_tile<kBatchConfRows>(items[wi.item].conf, wi.k, wi.x, wi.y, tile);
 }
 
 template <bool kFill>

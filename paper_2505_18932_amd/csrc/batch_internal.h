@@ -8,6 +8,7 @@
 
 namespace gg {
 
+constexpr int kBatchConfRows = 4;  // of the confidence phase's tiles (conf_tile)
 constexpr int kLightCounters = 2;  // persistent phases: bin count, bin fill
 constexpr int kXcds = 8;           // each phase keeps one counter per XCD
 constexpr int kBatchCounters = kLightCounters * kXcds;

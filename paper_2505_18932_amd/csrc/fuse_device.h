@@ -105,9 +105,6 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
          ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32);
 }
 
-// Keeps the loads on their side of this point of the program.
-__device__ __forceinline__ void schedule_fence() { __builtin_amdgcn_sched_barrier(0); }
-
 // ---------------------------------------------------------------------------
 // samples of the wavefront's chunk
 

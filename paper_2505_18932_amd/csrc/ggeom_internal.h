@@ -91,6 +91,10 @@ __device__ __forceinline__ float2 bload2(__amdgpu_buffer_rsrc_t r, uint32_t off)
   return make_float2(v.x, v.y);
 }
 
+__device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
+
 // The view table: per view Hs rows of Ws + 1 records, the last record of each
 // row (0, 0) -- no usable depth, no weight -- so that a sample whose column
 // falls outside the image may read that record instead of being tested.
@@ -316,7 +320,7 @@ int launch_network_inputs(const NetArgs &a, hipStream_t s);
 int launch_blend(const BlendArgs &a, hipStream_t s);
 
 int launch_bins(const gg_tsdf_params &p, float2 *bins, uint32_t *cells, uint32_t ncells,
-                hipStream_t s);
+                bool ranges, hipStream_t s);
 int launch_conf(const ConfArgs &a, hipStream_t s);
 int launch_integrate(const IntegrateArgs &a, hipStream_t s);
 // Which form of the fusion kernel a launch takes (bits of its template arguments).

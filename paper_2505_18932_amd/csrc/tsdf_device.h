@@ -33,106 +33,138 @@ __device__ __forceinline__ float2 bin_record(int d, int D, float z_near, float z
 // ---------------------------------------------------------------------------
 // fusion weight (Suppl. A.1)
 
+// Keeps the loads on their side of this point of the program.
+__device__ __forceinline__ void schedule_fence() { __builtin_amdgcn_sched_barrier(0); }
+
+// A tile of the window kernels: 32 x 8 kRows pixels, thread (x, y) of 32 x 8
+// with the kRows pixels from row kRows y down.
 constexpr int kConfTX = 32, kConfTY = 8, kMaxR = (GG_MAX_WINDOW - 1) / 2;
-constexpr int kConfLW = kConfTX + 2 * kMaxR, kConfLH = kConfTY + 2 * kMaxR;
+constexpr int kConfLW = kConfTX + 2 * kMaxR;
+constexpr int conf_lds(int rows) { return (kConfTY * rows + 2 * kMaxR) * kConfLW; }  // floats
 // the staged tile, then two floats per row of 16 lanes
 constexpr int kConfRows = kConfTX * kConfTY / 16;
-constexpr int kConfTileFloats = kConfLH * kConfLW + 2 * kConfRows;
+constexpr int conf_tile_floats(int rows) { return conf_lds(rows) + 2 * kConfRows; }
 
-// nu of Suppl. A.1 at pixel (i, j) with centre depth dq, reading the staged
-// tile (origin at image (i0 - r, j0 - r)); row-major over the window.
-__device__ __forceinline__ float window_nu(const float *tile, int li, int lj, int i, int j,
-                                           float dq, const ConfArgs &a) {
-  const int r = a.radius;
-  float nu = 0.0f;
-  for (int dy = -r; dy <= r; ++dy) {
-    const int jj = j + dy;
-    if (jj < 0 || jj >= a.Hs) continue;
-    for (int dx = -r; dx <= r; ++dx) {
-      const int ii = i + dx;
-      if (ii < 0 || ii >= a.Ws) continue;
-      const float dn = tile[(lj + dy) * kConfLW + (li + dx)];
-      float term;
-      if (depth_ok(dn)) {
-        const float dd = dq - dn;
-        term = fminf(dd * dd, a.tw2);
-      } else {
-        term = a.tw2;
-      }
-      nu = nu + term;
-    }
-  }
-  return nu;
-}
-
-// nu for a pixel whose whole window lies inside the image (radius R known
-// at compile time): the same terms in the same row-major order, with holes
-// staged as NaN -- d_q - NaN is NaN and fminf(NaN, tau^2) = tau^2, which is
-// exactly a hole's term -- so no test is needed per neighbour.
-template <int R>
-__device__ __forceinline__ float window_nu_interior(const float *tile, int li, int lj, float dq,
-                                                    float tw2) {
+// nu of Suppl. A.1 (window radius R) of kRows pixels one below the other,
+// centre depths dq, the first at (li, lj) of the staged tile; each pixel's
+// terms in row-major order.  A staged row is read once for all the pixels
+// whose window it crosses.  Holes are staged as NaN -- dq - NaN is NaN and
+// fminf(NaN, tau^2) = tau^2, exactly a hole's term -- and pixels outside the
+// image as -1: kEdge drops their terms (+0 changes no sum); a tile whose
+// windows all lie inside the image has none.
+template <int R, int kRows, bool kEdge>
+__device__ __forceinline__ void window_rows(const float *tile, int li, int lj,
+                                            const float (&dq)[kRows], float tw2,
+                                            float (&nu)[kRows]) {
   const float *w = tile + (lj - R) * kConfLW + (li - R);
-  float nu = 0.0f;
 #pragma unroll
-  for (int dy = 0; dy <= 2 * R; ++dy)
+  for (int r = 0; r < kRows; ++r) nu[r] = 0.0f;
 #pragma unroll
-    for (int dx = 0; dx <= 2 * R; ++dx) {
-      const float dd = dq - w[dy * kConfLW + dx];
-      nu = nu + fminf(dd * dd, tw2);
+  for (int y = 0; y < kRows + 2 * R; ++y) {
+    float dn[2 * R + 1];
+#pragma unroll
+    for (int dx = 0; dx <= 2 * R; ++dx) dn[dx] = w[y * kConfLW + dx];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      if (y < r || y > r + 2 * R) continue;
+#pragma unroll
+      for (int dx = 0; dx <= 2 * R; ++dx) {
+        const float dd = dq[r] - dn[dx];
+        const float term = fminf(dd * dd, tw2);
+        nu[r] = nu[r] + (kEdge && dn[dx] < 0.0f ? 0.0f : term);
+      }
     }
-  return nu;
-}
-
-__device__ __forceinline__ float window_nu_fast(const float *tile, int li, int lj, float dq,
-                                                const ConfArgs &a) {
-  switch (a.radius) {
-    case 0: return window_nu_interior<0>(tile, li, lj, dq, a.tw2);
-    case 1: return window_nu_interior<1>(tile, li, lj, dq, a.tw2);
-    case 2: return window_nu_interior<2>(tile, li, lj, dq, a.tw2);
-    case 3: return window_nu_interior<3>(tile, li, lj, dq, a.tw2);
-    case 4: return window_nu_interior<4>(tile, li, lj, dq, a.tw2);
-    case 5: return window_nu_interior<5>(tile, li, lj, dq, a.tw2);
-    case 6: return window_nu_interior<6>(tile, li, lj, dq, a.tw2);
-    default: return window_nu_interior<kMaxR>(tile, li, lj, dq, a.tw2);
   }
 }
 
-// The window's tile staged in LDS; pixels without a usable depth are staged
-// as NaN (both window forms treat NaN as a hole), pixels outside the image
-// as 0 (only the bounds-checked form can reach them, and it skips them).
-// A staged row is at most 46 floats: one wavefront's lanes take its columns
-// and the workgroup's wavefronts (blockDim a multiple of 64) step down the
-// rows, so no lane divides by the row width.  kDepth: the source is a depth
-// map, whose holes are staged as NaN; otherwise values are staged as read.
-template <bool kDepth>
+template <int R, int kRows>
+__device__ __forceinline__ void window_nu_r(const float *tile, bool edge, int li, int lj,
+                                            const float (&dq)[kRows], float tw2,
+                                            float (&nu)[kRows]) {
+  if constexpr (R <= 3) {
+    if (edge)
+      window_rows<R, kRows, true>(tile, li, lj, dq, tw2, nu);
+    else
+      window_rows<R, kRows, false>(tile, li, lj, dq, tw2, nu);
+  } else {  // a pixel at a time: the code of the larger windows stays within the cache
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const float d[1] = {dq[r]};
+      float n[1];
+      if (edge)
+        window_rows<R, 1, true>(tile, li, lj + r, d, tw2, n);
+      else
+        window_rows<R, 1, false>(tile, li, lj + r, d, tw2, n);
+      nu[r] = n[0];
+    }
+  }
+}
+
+template <int kRows>
+__device__ __forceinline__ void window_nu(const float *tile, bool edge, int li, int lj,
+                                          const float (&dq)[kRows], const ConfArgs &a,
+                                          float (&nu)[kRows]) {
+  switch (a.radius) {
+    case 0: return window_nu_r<0>(tile, edge, li, lj, dq, a.tw2, nu);
+    case 1: return window_nu_r<1>(tile, edge, li, lj, dq, a.tw2, nu);
+    case 2: return window_nu_r<2>(tile, edge, li, lj, dq, a.tw2, nu);
+    case 3: return window_nu_r<3>(tile, edge, li, lj, dq, a.tw2, nu);
+    case 4: return window_nu_r<4>(tile, edge, li, lj, dq, a.tw2, nu);
+    case 5: return window_nu_r<5>(tile, edge, li, lj, dq, a.tw2, nu);
+    case 6: return window_nu_r<6>(tile, edge, li, lj, dq, a.tw2, nu);
+    default: return window_nu_r<kMaxR>(tile, edge, li, lj, dq, a.tw2, nu);
+  }
+}
+
+// Whether a tile's windows reach past the image.
+template <int kRows>
+__device__ __forceinline__ bool tile_at_edge(const ConfArgs &a, int i0, int j0) {
+  return i0 < a.radius || j0 < a.radius || i0 + kConfTX + a.radius > a.Ws ||
+         j0 + kConfTY * kRows + a.radius > a.Hs;
+}
+
+// The windows of a tile staged in LDS.  A depth map's pixels without a usable
+// depth are staged as NaN, places outside the image as -1 (kDepths) or NaN as
+// well (kNeighbours); of another map twice the value, and 0.  A staged row
+// is at most 46 floats: one wavefront's lanes take its columns and the
+// workgroup's four wavefronts step down the rows, so no lane divides by the
+// row width; four or five rows' loads are in flight together.
+enum : int { kDepths, kNeighbours, kTwice };
+template <int kWhat, int kRows>
 __device__ __forceinline__ void stage_rows(float *tile, const float *src, int i0, int j0,
                                            const ConfArgs &a) {
   static_assert(kConfTX + 2 * kMaxR <= 64, "a staged row fits one wavefront");
+  constexpr int kBatch = kRows == 1 ? 4 : 5;
   const int r = a.radius;
-  const int tw = kConfTX + 2 * r, th = kConfTY + 2 * r;
-  const int lx = (int)(threadIdx.x & 63u), waves = (int)(blockDim.x >> 6);
+  const int tw = kConfTX + 2 * r, th = kConfTY * kRows + 2 * r;
+  const int lx = (int)(threadIdx.x & 63u);
+  const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int gi = i0 - r + lx;
-  const bool in_col = gi >= 0 && gi < a.Ws;
+  const bool in_col = lx < tw && gi >= 0 && gi < a.Ws;
+  // at most 16384 x 16384 pixels (host check)
+  const auto image = buffer_of(src, (uint32_t)a.Ws * (uint32_t)a.Hs * 4u);
   // stored at (ly + kMaxR - r, lx + kMaxR - r) so that window offsets are
   // relative to the fixed centre origin
   float *dst = tile + (kMaxR - r) * kConfLW + (lx + kMaxR - r);
-  if (lx < tw) {
-    for (int ly = (int)(threadIdx.x >> 6); ly < th; ly += waves) {
-      const int gj = j0 - r + ly;
-      float v = 0.0f;
-      if (in_col && gj >= 0 && gj < a.Hs) {
-        v = gmem(src)[(size_t)gj * a.Ws + gi];
-        if (kDepth && !depth_ok(v)) v = __builtin_nanf("");
-      }
-      dst[ly * kConfLW] = v;
+  for (int y0 = wave; y0 < th; y0 += 4 * kBatch) {
+    float v[kBatch];
+#pragma unroll
+    for (int n = 0; n < kBatch; ++n) {
+      const int gj = j0 - r + y0 + 4 * n;
+      const bool in = in_col && gj >= 0 && gj < a.Hs;
+      v[n] = bload1(image, in ? ((uint32_t)gj * (uint32_t)a.Ws + (uint32_t)gi) * 4u : kOutOfRange);
+      if (kWhat == kTwice)
+        v[n] = v[n] * 2.0f;
+      else if (!depth_ok(v[n]))
+        v[n] = __builtin_nanf("");
+      if (kWhat == kDepths && !in) v[n] = -1.0f;
+    }
+    if (lx < tw) {
+#pragma unroll
+      for (int n = 0; n < kBatch; ++n)
+        if (y0 + 4 * n < th) dst[(y0 + 4 * n) * kConfLW] = v[n];
     }
   }
-}
-
-__device__ __forceinline__ void stage_tile(float *tile, const float *dk, int i0, int j0,
-                                           const ConfArgs &a) {
-  stage_rows<true>(tile, dk, i0, j0, a);
 }
 
 // The largest value of each row of 16 lanes, in all of them (lane swizzles of
@@ -148,19 +180,19 @@ __device__ __forceinline__ float row_max(float v) {
   return fmaxf(v, row_swizzle<0x140>(v));  // row mirror
 }
 
-// Start value of word i of ConfArgs::cells.
-__device__ __forceinline__ uint32_t cell_start(uint32_t i, uint32_t ncells) {
-  return i < ncells ? 0u : 0x7f800000u;
+// Start value of word i of ConfArgs::cells: the empty range, for ranges to be formed, or the
+// range of every depth.
+__device__ __forceinline__ uint32_t cell_start(uint32_t i, uint32_t ncells, bool ranges) {
+  return (i < ncells) == ranges ? 0u : 0x7f800000u;
 }
 
 // The tile's largest and least usable depth into every 3 x 3 window of cells
 // that holds the tile's cell (float bits of non-negative values order as
 // integers).  A tile lies in one cell: tiles are kCell wide and divide it in
-// height.  d: the thread's depth, 0 if it has none.
-__device__ __forceinline__ void cell_range(const ConfArgs &a, int k, int i0, int j0, float d,
-                                           float *red) {
-  static_assert(kConfTX == kCell && kCell % kConfTY == 0, "a tile lies in one cell");
-  const float hi = row_max(d), lo = -row_max(d > 0.0f ? -d : -INFINITY);
+// height.  The thread's largest depth, 0 if it has none, and its least, inf.
+__device__ __forceinline__ void cell_range(const ConfArgs &a, int k, int i0, int j0, float dmax,
+                                           float dmin, float *red) {
+  const float hi = row_max(dmax), lo = -row_max(-dmin);
   if ((threadIdx.x & 15u) == 0) {
     red[threadIdx.x >> 4] = hi;
     red[kConfRows + (threadIdx.x >> 4)] = lo;
@@ -185,34 +217,35 @@ __device__ __forceinline__ void cell_range(const ConfArgs &a, int k, int i0, int
   }
 }
 
-// One 32 x 8 tile (bx, by) of view k; tile: LDS of kConfTileFloats floats.
+// One 32 x 8 kRows tile (bx, by) of view k; tile: LDS of conf_tile_floats(kRows) floats.
+template <int kRows>
 __device__ __forceinline__ void conf_tile(const ConfArgs &a, int k, int bx, int by, float *tile) {
-  const int i0 = bx * kConfTX, j0 = by * kConfTY;
-  const float *dk = a.depth + (size_t)k * a.Ws * a.Hs;
-  stage_tile(tile, dk, i0, j0, a);
+  static_assert(kConfTX == kCell && kCell % (kConfTY * kRows) == 0, "a tile lies in one cell");
+  const int i0 = bx * kConfTX, j0 = by * kConfTY * kRows;
+  stage_rows<kDepths, kRows>(tile, a.depth + (size_t)k * a.Ws * a.Hs, i0, j0, a);
   __syncthreads();
-  const int lx = threadIdx.x & (kConfTX - 1), ly = threadIdx.x / kConfTX;
+  const int lx = threadIdx.x & (kConfTX - 1), ly = threadIdx.x / kConfTX * kRows;
   const int i = i0 + lx, j = j0 + ly;
-  // every window of the tile inside the image: the unchecked form
-  const bool interior = i0 >= a.radius && j0 >= a.radius &&
-                        i0 + kConfTX + a.radius <= a.Ws && j0 + kConfTY + a.radius <= a.Hs;
-  float dusable = 0.0f;
-  if (ly < kConfTY && i < a.Ws && j < a.Hs) {
-    const int li = lx + kMaxR, lj = ly + kMaxR;
-    const float dq = tile[lj * kConfLW + li];
+  const int li = lx + kMaxR, lj = ly + kMaxR;
+  float dq[kRows], nu[kRows], dmax = 0.0f, dmin = INFINITY;
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) dq[r] = tile[(lj + r) * kConfLW + li];
+  window_nu<kRows>(tile, tile_at_edge<kRows>(a, i0, j0), li, lj, dq, a, nu);
+  float2 *row = a.table + (size_t)k * table_view_records(a.Ws, a.Hs) + (size_t)j * table_pitch(a.Ws);
+#pragma unroll
+  for (int r = 0; r < kRows; ++r, row += table_pitch(a.Ws)) {
+    if (i >= a.Ws || j + r >= a.Hs) continue;
     float2 rec = make_float2(-INFINITY, 0.0f);
-    if (depth_ok(dq)) {
-      const float nu = interior ? window_nu_fast(tile, li, lj, dq, a)
-                                : window_nu(tile, li, lj, i, j, dq, a);
-      const float om = (nu == 0.0f) ? 1.0f : fminf(a.scale / sqrtf(nu / a.n2), 1.0f);
-      rec = make_float2(dq, om);
-      dusable = dq;
+    if (depth_ok(dq[r])) {
+      const float om = (nu[r] == 0.0f) ? 1.0f : fminf(a.scale / sqrtf(nu[r] / a.n2), 1.0f);
+      rec = make_float2(dq[r], om);
+      dmax = fmaxf(dmax, dq[r]);
+      dmin = fminf(dmin, dq[r]);
     }
-    float2 *row = a.table + (size_t)k * table_view_records(a.Ws, a.Hs) + (size_t)j * table_pitch(a.Ws);
     gstore2(row + i, rec);
     if (i == a.Ws - 1) gstore2(row + a.Ws, make_float2(0.0f, 0.0f));  // the row's closing record
   }
-  if (a.cells) cell_range(a, k, i0, j0, dusable, tile + kConfLH * kConfLW);
+  if (a.cells) cell_range(a, k, i0, j0, dmax, dmin, tile + conf_lds(kRows));
 }
 
 // Fusion tile at position s of the launch's visiting order.  Far source
