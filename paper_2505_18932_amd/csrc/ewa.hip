@@ -13,10 +13,10 @@
 //            each touched tile's segment (in arrival order);
 //   raster - one wavefront per (view, tile): the tile's keys are sorted in
 //            ascending (z, source index) order -- a bitonic sort in LDS for
-//            lists of up to sort_limit keys, else LDS-sorted runs merged
-//            pairwise in global memory -- and each lane composites its pixel
-//            front to back over the sorted list, 64 records at a time staged
-//            through LDS, until every lane has stopped.
+//            lists of up to sort_limit keys, else LDS-sorted runs of which
+//            each batch takes the 64 least keys -- and each lane composites
+//            its pixel front to back over the sorted list, 64 records at a
+//            time staged through LDS, until every lane has stopped.
 // The order of the terms is fixed by the keys, so the arrival order of the
 // fill does not matter: outputs are bitwise reproducible.  Every
 // floating-point step follows the operation order of the definition (the
@@ -199,13 +199,17 @@ constexpr int kEwaBlocksX = kEwaTile / kEwaBlock;
 constexpr int kEwaBlocks = kEwaBlocksX * kEwaBlocksX;
 constexpr int kEwaBlockLanes = kEwaBlock * kEwaBlock;
 
-struct EwaLds {
+// The keys leave LDS for registers before the first record is staged: 4.1 KB
+// instead of 7.4, and eight wavefronts per SIMD instead of five.
+union EwaLds {
   unsigned long long key[kEwaSortCap];
-  float4 rec[2][64];
-  float z[64];
-  // per block of the tile: the staged entries that may reach it, in order;
-  // slot 64 takes the writes of the lanes whose entry does not
-  uint8_t idx[kEwaBlocks][65];
+  struct {
+    float4 rec[2][64];
+    float z[64];
+    // per block of the tile: the staged entries that may reach it, in order;
+    // slot 64 takes the writes of the lanes whose entry does not
+    uint8_t idx[kEwaBlocks][65];
+  } b;
 };
 
 // Ascending bitonic sort of L.key[0 .. N) (N a power of two, 64 <= N <=
@@ -232,25 +236,35 @@ __device__ __forceinline__ uint32_t pow2_at_least(uint32_t n) {
   return N;
 }
 
-// Sort keys[0 .. m) (m > sort_limit) in global memory: runs of `chunk`
-// keys sorted in LDS, then pairwise merges between keys and alt, each lane
-// producing an equal share of every merged run (merge path).  Returns the
-// buffer that holds the sorted list.
-__device__ const unsigned long long *global_sort(EwaLds &L, unsigned long long *keys,
-                                                 unsigned long long *alt, uint32_t m,
-                                                 uint32_t chunk, uint32_t lane) {
+// Keys of one list longer than sort_limit: sorted runs of `width` keys at
+// keys, merged as they are taken.
+constexpr uint32_t kEwaRuns = 8;
+struct EwaRuns {
+  const unsigned long long *keys;
+  uint32_t width;
+  uint32_t head[kEwaRuns];  // wave-uniform
+};
+
+// Sorts keys[0 .. m) (m > sort_limit) into at most kEwaRuns runs in global
+// memory: runs of `chunk` keys sorted in LDS and, where these are more,
+// merged pairwise between keys and alt, each lane producing an equal share of
+// every merged run (merge path).
+__device__ __forceinline__ void sort_runs(EwaLds &L, unsigned long long *keys,
+                                          unsigned long long *alt, uint32_t m, uint32_t chunk,
+                                          uint32_t lane, EwaRuns &runs) {
   for (uint32_t base = 0; base < m; base += chunk) {
-    const uint32_t n = min(chunk, m - base);
-    for (uint32_t t = lane; t < chunk; t += 64) L.key[t] = t < n ? gmem(keys)[base + t] : ~0ull;
+    const uint32_t n = min(chunk, m - base), N = min(chunk, pow2_at_least(n));
+    for (uint32_t t = lane; t < N; t += 64) L.key[t] = t < n ? gmem(keys)[base + t] : ~0ull;
     __syncthreads();
-    lds_bitonic(L, chunk, lane);
+    lds_bitonic(L, N, lane);
     for (uint32_t t = lane; t < n; t += 64) gmem(keys)[base + t] = L.key[t];
     __syncthreads();
   }
   __threadfence();
   __syncthreads();
   unsigned long long *src = keys, *dst = alt;
-  for (uint32_t w = chunk; w < m; w <<= 1) {
+  uint32_t w = chunk;
+  for (; m > kEwaRuns * w; w <<= 1) {
     for (uint32_t lo = 0; lo < m; lo += 2 * w) {
       const uint32_t na = min(w, m - lo);
       const uint32_t nb = m - lo > w ? min(w, m - lo - w) : 0u;
@@ -280,43 +294,87 @@ __device__ const unsigned long long *global_sort(EwaLds &L, unsigned long long *
     src = dst;
     dst = t;
   }
-  return src;
+  runs.keys = src;
+  runs.width = w;
+#pragma unroll
+  for (uint32_t r = 0; r < kEwaRuns; ++r) runs.head[r] = r * w;
 }
 
-// The blocks of the tile (origin (tx0, ty0)) at whose pixels the Gaussian of
-// a staged record may take a term, as a bit mask (bit b: block b).  A term
-// needs alpha >= 1/255, so d^T S^-1 d <= 2 ln 255 < 11.1 and |dx| <=
-// sqrt(11.1 S_xx), and it needs |dx| <= rmax.  S_xx = M_yy / det M of the
-// conic M = S^-1, whose entries the record holds as Ah = -M_xx / 2, Ch =
-// -M_yy / 2, Bn = -M_xy; the extent takes 2% and a quarter pixel of margin
-// for the rounding of this reconstruction (the hardware's reciprocal and
-// square root, within an ulp or two, are well inside it) and of the tests
-// (a conic so ill-conditioned that S_xx comes out negative, infinite or NaN
-// falls back to rmax: fminf drops the NaN).  The test is a superset, so it
-// never decides a term: skipping a record it rejects leaves every pixel of
-// the block exactly as taking it would.  It is separable: a block's column
-// decides the x half, its row the y half.
-__device__ __forceinline__ uint32_t ewa_reach(float4 A, float4 B, float rmax, float tx0,
+// The 64 least of two ascending lists of 64 keys, ascending over the lanes.
+__device__ __forceinline__ unsigned long long merge_least(unsigned long long a,
+                                                          unsigned long long b, uint32_t lane) {
+  const unsigned long long r = __shfl_xor(b, 63);
+  unsigned long long x = a < r ? a : r;  // first up, then down
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) {
+    const unsigned long long y = __shfl_xor(x, s);
+    x = ((x < y) == ((lane & (uint32_t)s) == 0)) ? x : y;
+  }
+  return x;
+}
+
+// The next 64 keys of the list, ascending over the lanes (~0 past the end):
+// the least of the runs' next 64 each.  A list is composited only until its
+// pixels have stopped, so the rest is never merged (measured, 4 x 1352 x 1014
+// with 2% of the lists longer than 512 keys: 772 us for the kernel with full
+// merges, 517 if they were free).
+__device__ __forceinline__ unsigned long long next_keys(EwaRuns &runs, uint32_t m, uint32_t lane) {
+  unsigned long long k[kEwaRuns], least = ~0ull;
+#pragma unroll
+  for (uint32_t r = 0; r < kEwaRuns; ++r) {
+    k[r] = ~0ull;
+    if (r * runs.width < m) {
+      const uint32_t at = runs.head[r] + lane;
+      if (at < min(m, (r + 1) * runs.width)) k[r] = gmem(runs.keys)[at];
+    }
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < kEwaRuns; ++r)
+    if (r * runs.width < m) least = r ? merge_least(least, k[r], lane) : k[r];
+  const unsigned long long last = __shfl(least, 63);
+#pragma unroll
+  for (uint32_t r = 0; r < kEwaRuns; ++r)
+    runs.head[r] += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(k[r] <= last && k[r] != ~0ull));
+  return least;
+}
+
+// Where the Gaussian of a staged record may take a term: within a circle and
+// a square.  A term needs alpha >= 1/255, so d^T M d <= 2 ln 255 < 11.1 with
+// the conic M, whose entries the record holds as Ah = -M_xx / 2, Ch = -M_yy /
+// 2, Bn = -M_xy; hence |d|^2 <= 11.1 l, l = l_max(M) / det M the larger
+// eigenvalue of M^-1.  And it needs |dx|, |dy| <= rmax.  The circle takes 2%
+// and both take 1/16 pixel of margin for the rounding of this reconstruction
+// (det within 2^-12 of its value, as det >= 2^-10 M_xx M_yy, else there is no
+// circle; the hardware's reciprocal and square root within an ulp or two) and
+// of the tests.  The test is a superset, so it never decides a term: skipping
+// a record it rejects leaves every pixel of the block exactly as taking it
+// would.  (The circle's square alone takes a third more records.)
+struct EwaReach {
+  float x2[kEwaBlocksX], y2[kEwaBlocksX], r2;  // a block's least squared distance: x2 + y2
+};
+
+__device__ __forceinline__ EwaReach ewa_reach(float4 A, float4 B, float rmax, float tx0,
                                               float ty0) {
-  const float det = 4.0f * (A.z * B.x) - A.w * A.w;
-  const float rdet = __builtin_amdgcn_rcpf(det);
-  const float sxx = (-2.0f * B.x) * rdet, syy = (-2.0f * A.z) * rdet;
-  const float hx = fminf(__builtin_amdgcn_sqrtf(11.32f * sxx), rmax) + 0.25f;
-  const float hy = fminf(__builtin_amdgcn_sqrtf(11.32f * syy), rmax) + 0.25f;
-  // pixel centres q + 0.5 .. q + kEwaBlock - 0.5 against u +- h
+  EwaReach e;
+  const float prod = 4.0f * (A.z * B.x), det = prod - A.w * A.w;
+  const float dif = B.x - A.z;
+  const float l = (__builtin_amdgcn_sqrtf(dif * dif + A.w * A.w) - (A.z + B.x)) *
+                  __builtin_amdgcn_rcpf(det);
+  const float r = __builtin_amdgcn_sqrtf(11.32f * l) + 0.0625f;
+  const bool circle = det >= 0x1p-10f * prod && r < INFINITY;  // false for NaN
+  e.r2 = circle ? r * r : 0x1p60f;
+  const float clip = rmax + 0.0625f;
+  // pixel centres q + 0.5 .. q + kEwaBlock - 0.5
   constexpr float kLast = (float)kEwaBlock - 0.5f;
-  uint32_t cols = 0, rows = 0;
 #pragma unroll
   for (int c = 0; c < kEwaBlocksX; ++c) {
     const float qx = tx0 + (float)(kEwaBlock * c), qy = ty0 + (float)(kEwaBlock * c);
-    if ((qx + 0.5f) - A.x <= hx && A.x - (qx + kLast) <= hx) cols |= 1u << c;
-    if ((qy + 0.5f) - A.y <= hy && A.y - (qy + kLast) <= hy) rows |= 1u << c;
+    const float dx = fmaxf(fmaxf((qx + 0.5f) - A.x, A.x - (qx + kLast)), 0.0f);
+    const float dy = fmaxf(fmaxf((qy + 0.5f) - A.y, A.y - (qy + kLast)), 0.0f);
+    e.x2[c] = dx <= clip ? dx * dx : INFINITY;
+    e.y2[c] = dy <= clip ? dy * dy : INFINITY;
   }
-  uint32_t reach = 0;
-#pragma unroll
-  for (int r = 0; r < kEwaBlocksX; ++r)
-    if ((rows >> r) & 1u) reach |= cols << (kEwaBlocksX * r);
-  return reach;
+  return e;
 }
 
 // One wavefront per (view, tile); its 64 lanes are the tile's blocks of
@@ -325,11 +383,16 @@ __device__ __forceinline__ uint32_t ewa_reach(float4 A, float4 B, float rmax, fl
 // records is culled per block (ewa_reach) into an ordered list, and each
 // block's lanes composite only their own list: the wavefront takes as many
 // steps as the longest list instead of all 64, and every pixel still sees,
-// front to back, every record that can touch it.
-__global__ __launch_bounds__(64) void ewa_raster_kernel(EwaArgs a) {
+// front to back, every record that can touch it.  Tiles go to the XCDs in
+// turn: long lists lie together (slanted surfaces, silhouettes), and parts of
+// the image per XCD left some of them idle (492 us against 446, the shared
+// records notwithstanding).  Measured, 4 x 1352 x 1014 (lists of 114 keys on
+// average, 2% above 512, at most 1778): 772 us with full merges, a square cull
+// and 7.4 KB of LDS, 446 now; 2 x 320 x 240 46 and 39.
+__global__ __launch_bounds__(64, 6) void ewa_raster_kernel(EwaArgs a) {
   __shared__ EwaLds L;
   const int k = blockIdx.y;
-  const uint32_t tile = xcd_tile(blockIdx.x, a.ntiles);
+  const uint32_t tile = blockIdx.x;
   const uint32_t lane = threadIdx.x;
   const uint32_t ty = tile / (uint32_t)a.ntx, tx = tile - ty * (uint32_t)a.ntx;
   const uint32_t blk = lane / kEwaBlockLanes, ql = lane % kEwaBlockLanes;
@@ -339,18 +402,26 @@ __global__ __launch_bounds__(64) void ewa_raster_kernel(EwaArgs a) {
   const size_t seg = (size_t)k * a.ntiles + tile;
   const uint32_t off = min(gmem(a.tile_offset)[seg], a.cap);
   const uint32_t m = min(gmem(a.tile_count)[seg], a.cap - off);
-  const unsigned long long *list = nullptr;
   const bool in_lds = m <= a.sort_limit;
+  constexpr uint32_t kHeld = kEwaSortCap / 64;
+  unsigned long long held[kHeld];  // a list sorted in LDS: entries 64 i + lane
+  EwaRuns runs{};
+#pragma unroll
+  for (uint32_t i = 0; i < kHeld; ++i) held[i] = ~0ull;
   if (m > 0) {
     if (in_lds) {
       const uint32_t N = pow2_at_least(m);
       for (uint32_t t = lane; t < N; t += 64) L.key[t] = t < m ? gmem(a.keys)[off + t] : ~0ull;
       __syncthreads();
       lds_bitonic(L, N, lane);
+#pragma unroll
+      for (uint32_t i = 0; i < kHeld; ++i)
+        if (64 * i < m) held[i] = L.key[64 * i + lane];
+      __syncthreads();
     } else {
       uint32_t chunk = 64;
       while (chunk * 2 <= a.sort_limit) chunk <<= 1;
-      list = global_sort(L, a.keys + off, a.keys_alt + off, m, chunk, lane);
+      sort_runs(L, a.keys + off, a.keys_alt + off, m, chunk, lane, runs);
     }
   }
   const float px = (float)x + 0.5f, py = (float)y + 0.5f;
@@ -361,24 +432,33 @@ __global__ __launch_bounds__(64) void ewa_raster_kernel(EwaArgs a) {
   const float tx0 = (float)((int)tx * kEwaTile), ty0 = (float)((int)ty * kEwaTile);
   for (uint32_t base = 0; base < m; base += 64) {
     if (__all(done)) break;
-    const uint32_t e = base + lane;
-    uint32_t reach = 0;  // bit b: the record may reach block b
-    if (e < m) {
-      const unsigned long long key = in_lds ? L.key[e] : gmem(list)[e];
+    unsigned long long key;
+    if (in_lds) {
+      key = held[0];
+#pragma unroll
+      for (uint32_t i = 0; i + 1 < kHeld; ++i) held[i] = held[i + 1];
+    } else {
+      key = next_keys(runs, m, lane);
+    }
+    EwaReach reach;
+    reach.r2 = -1.0f;
+#pragma unroll
+    for (int c = 0; c < kEwaBlocksX; ++c) reach.x2[c] = reach.y2[c] = 0.0f;
+    if (base + lane < m) {
       const uint32_t q = (uint32_t)key;
       const gg_v4f r0 = *(const GG_GLOBAL gg_v4f *)(rec + 2 * (size_t)q);
       const gg_v4f r1 = *(const GG_GLOBAL gg_v4f *)(rec + 2 * (size_t)q + 1);
       const float4 A = make_float4(r0.x, r0.y, r0.z, r0.w), B = make_float4(r1.x, r1.y, r1.z, r1.w);
-      L.rec[0][lane] = A;
-      L.rec[1][lane] = B;
-      L.z[lane] = __uint_as_float((uint32_t)(key >> 32));
+      L.b.rec[0][lane] = A;
+      L.b.rec[1][lane] = B;
+      L.b.z[lane] = __uint_as_float((uint32_t)(key >> 32));
       reach = ewa_reach(A, B, rmax, tx0, ty0);
     }
     // each block's list: the records that reach it, in staging (= front to back) order
     int counts = 0;  // lane b (< kEwaBlocks): the length of block b's list
 #pragma unroll
     for (uint32_t qd = 0; qd < (uint32_t)kEwaBlocks; ++qd) {
-      const bool hit = (reach & (1u << qd)) != 0u;
+      const bool hit = reach.x2[qd % kEwaBlocksX] + reach.y2[qd / kEwaBlocksX] <= reach.r2;
       const unsigned long long b = __builtin_amdgcn_ballot_w64(hit);
       // the lane's rank among the hits: set bits of b below the lane
       const uint32_t rank =
@@ -386,23 +466,29 @@ __global__ __launch_bounds__(64) void ewa_raster_kernel(EwaArgs a) {
       // every lane stores (no branch): a hit at its rank, the others into the
       // row's spare slot, which nothing reads (relaxed atomic stores, as
       // several lanes store to it at once)
-      __hip_atomic_store(&L.idx[qd][hit ? rank : 64u], (uint8_t)lane, __ATOMIC_RELAXED,
+      __hip_atomic_store(&L.b.idx[qd][hit ? rank : 64u], (uint8_t)lane, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_WORKGROUP);
       counts = gg_writelane(__popcll(b), (int)qd, counts);
     }
     const uint32_t nq = (uint32_t)__shfl(counts, (int)blk);
     __syncthreads();
-    // each block walks its own list; the wavefront runs as long as the longest
-    for (uint32_t s = 0; s < nq; ++s) {
-      const uint32_t t = L.idx[blk][s];
-      const float4 A = L.rec[0][t], B = L.rec[1][t];
+    // each block walks its own list; the wavefront runs as long as the
+    // longest.  A step's record is read during the step before (entries past
+    // the list's end are read as some staged record's, and not used).
+    uint32_t t = L.b.idx[blk][0] & 63u;
+    float4 A = L.b.rec[0][t], B = L.b.rec[1][t];
+    float z = L.b.z[t];
+    t = L.b.idx[blk][1] & 63u;
+    for (uint32_t s = 0; s < nq && !done; ++s) {
+      const float4 An = L.b.rec[0][t], Bn = L.b.rec[1][t];
+      const float zn = L.b.z[t];
+      t = L.b.idx[blk][min(s + 2u, 63u)] & 63u;
       const float dx = px - A.x, dy = py - A.y;
       const bool in = fabsf(dx) <= rmax && fabsf(dy) <= rmax;
       const float power = fmaf(A.w, dx * dy, fmaf(A.z, dx * dx, B.x * (dy * dy)));
-      const float z = L.z[t];
       const float al = fminf(0.99f, exp_alpha(power));
       const float tt = T * (1.0f - al);
-      const bool take = !done && in && !(power > 0.0f) && !(al < amin);
+      const bool take = in && !(power > 0.0f) && !(al < amin);
       const bool stop = take && tt < 1e-4f;
       if (take && !stop) {
         const float w = al * T;
@@ -413,6 +499,9 @@ __global__ __launch_bounds__(64) void ewa_raster_kernel(EwaArgs a) {
         T = tt;
       }
       done = done || stop;
+      A = An;
+      B = Bn;
+      z = zn;
     }
     __syncthreads();
   }
