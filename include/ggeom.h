@@ -489,8 +489,7 @@ typedef struct gg_batch_item {
 /* Launch shape chosen by the autotuner (0 = default). */
 typedef struct gg_batch_tuning {
   int32_t pixels_per_block; /* 0..1024 (the fusion's workgroups hold 64 pixels)            */
-  int32_t blocks_per_cu;   /* resident workgroups per compute unit of the persistent splat
-                              binning phases, 0..64 (0: as many as fit)                    */
+  int32_t blocks_per_cu;   /* 0..64 (no kernel takes it)                                   */
   int32_t bins_per_thread; /* of the fusion, as in gg_volume_tuning (0: default)            */
   int32_t branches;        /* 0 or 2: the splat phases form a branch of the graph that runs
                               beside the fusion; 1: every phase in one sequence          */

@@ -28,9 +28,9 @@ CACHE = os.path.join(HERE, "tuning_cache.json")
 # order in pixels); 0 = default.  The fusion's workgroup is fixed: its candidates are bands.
 PLAIN_CANDIDATES = [(0, 0, 0, 0), (0, 0, 0, 64), (0, 0, 0, 128), (0, 0, 0, 192), (0, 0, 0, 512),
                     (0, 0, 0, 65536)]
-# (pixels per fusion workgroup, resident workgroups per compute unit of the
-# persistent splat binning phases, bins per thread, graph branches); 0 = default
-BATCH_CANDIDATES = [(0, 0, 0, 2), (0, 0, 0, 1), (0, 1, 0, 2), (0, 2, 0, 2)]
+# (pixels per fusion workgroup, workgroups per compute unit, bins per thread, graph
+# branches); 0 = default.  Only the branches shape a plan.
+BATCH_CANDIDATES = [(0, 0, 0, 2), (0, 0, 0, 1)]
 
 
 def arch(device=None) -> str:

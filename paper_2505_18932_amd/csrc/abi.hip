@@ -1285,10 +1285,8 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
   if (ppb_t < 0 || ppb_t > 1024 || per_cu < 0 || per_cu > 64 || branches < 0 || branches > 2)
     return fail(GG_ERR_INVALID, "%s: pixels_per_block in 0..1024, blocks_per_cu in 0..64, "
                 "branches in 0..2", N);
-  int dev = 0, cus = 256;
+  int dev = 0;  // (there is one)
   if (int rc = check_hip(hipGetDevice(&dev), N)) return rc;
-  if (int rc = check_hip(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), N))
-    return rc;
 
   // host descriptors, work lists and the device-memory layout
   std::vector<BatchItem> h(n);
@@ -1356,7 +1354,7 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
     }
   }
   const size_t o_counts = off;
-  off += up256(4 * (count_words + kBatchCounters));
+  off += up256(4 * count_words);
   auto put = [&](size_t bytes) { const size_t o = off; off += up256(bytes ? bytes : 1); return o; };
   const size_t o_conf = put(sizeof(WorkItem) * conf.size()), o_bin = put(sizeof(WorkItem) * bin.size()),
                o_raster = put(sizeof(WorkItem) * raster.size());
@@ -1367,8 +1365,6 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
   gg_batch *b = new gg_batch();
   BatchPlan &P = b->P;
   P.n_items = n;
-  P.cus = cus;
-  P.blocks_per_cu = per_cu;
   P.branches = branches ? branches : 2;
   P.dev_bytes = off;
   if (int rc = check_hip(hipMalloc(&P.dev, off), N)) {
@@ -1421,8 +1417,7 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
   P.d_splat_items = (uint32_t *)(dv + o_sitems);
   P.n_splat_items = (uint32_t)splat_items.size();
   P.zero_ptr = (uint32_t *)(dv + o_counts);
-  P.zero_words = count_words + kBatchCounters;
-  P.d_ctr = P.zero_ptr + count_words;
+  P.zero_words = count_words;
   int rc = GG_OK;
   auto cp = [&](size_t o, const void *src, size_t bytes) {
     if (rc == GG_OK && bytes) rc = check_hip(hipMemcpy(dv + o, src, bytes, hipMemcpyHostToDevice), N);
@@ -1433,7 +1428,6 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
   cp(o_raster, raster.data(), sizeof(WorkItem) * raster.size());
   for (size_t g = 0; g < groups.size(); ++g)
     cp(o_integ[g], integ[g].data(), sizeof(WorkItem) * integ[g].size());
-  if (rc == GG_OK) rc = batch_occupancy(P);
   cp(o_sitems, splat_items.data(), 4 * splat_items.size());
   // capture every phase into one graph
   hipStream_t cs = nullptr, side = nullptr;

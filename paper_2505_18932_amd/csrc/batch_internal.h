@@ -9,9 +9,6 @@
 namespace gg {
 
 constexpr int kBatchConfRows = 4;  // of the confidence phase's tiles (conf_tile)
-constexpr int kLightCounters = 2;  // persistent phases: bin count, bin fill
-constexpr int kXcds = 8;           // each phase keeps one counter per XCD
-constexpr int kBatchCounters = kLightCounters * kXcds;
 
 // Everything one item's phases need, in device memory (read with scalar
 // loads: the descriptor address is uniform per work entry).
@@ -63,9 +60,7 @@ struct IntegGroup {
 
 struct BatchPlan {
   int32_t n_items = 0;
-  int cus = 256, blocks_per_cu = 0;  // 0: the binning phases fill each CU
-  int branches = 2;                  // 2: splat phases beside the fusion; 1: one sequence
-  int occ_bin = 1;  // resident workgroups per CU of the binning phases
+  int branches = 2;  // 2: splat phases beside the fusion; 1: one sequence
   // device memory owned by the plan
   void *dev = nullptr;
   size_t dev_bytes = 0;
@@ -75,10 +70,8 @@ struct BatchPlan {
   std::vector<IntegGroup> integ;
   uint32_t *d_splat_items = nullptr;
   uint32_t n_splat_items = 0;
-  uint32_t *zero_ptr = nullptr;  // tile counts of every item, then the counters
+  uint32_t *zero_ptr = nullptr;  // tile counts and list allocators of every item
   size_t zero_words = 0;
-  uint32_t *d_ctr = nullptr;     // kBatchCounters work counters of the binning phases
-                                 // (zeroed per launch): kXcds per phase
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -87,6 +80,5 @@ struct BatchPlan {
 // stream and the two events the splat phases become a parallel branch.
 int batch_record(BatchPlan &P, hipStream_t s, hipStream_t side, hipEvent_t fork,
                  hipEvent_t join);
-int batch_occupancy(BatchPlan &P);
 
 }  // namespace gg

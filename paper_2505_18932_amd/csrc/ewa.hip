@@ -6,9 +6,8 @@
 // Pipeline per call (all views at once):
 //   count  - every source pixel builds its Gaussian (target mean, conic,
 //            colour) into a record and counts the 8 x 8 target tiles its
-//            candidate window touches (wavefront-aggregated atomics);
-//   alloc  - a list segment per tile (wavefront prefix sums, one atomic per
-//            wavefront on an allocator; segments in atomic order);
+//            candidate window touches (one atomic per wavefront and tile);
+//   alloc  - a list segment per tile, as the splat's;
 //   fill   - the same walk writes the key bits(z) << 32 | source index into
 //            each touched tile's segment (in arrival order);
 //   raster - one wavefront per (view, tile): the tile's keys are sorted in
@@ -115,9 +114,8 @@ __global__ __launch_bounds__(256) void ewa_bin_kernel(EwaArgs a) {
   const uint32_t by = blockIdx.x / nbx, bx = blockIdx.x - by * nbx;
   const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
   const uint32_t i = bx * kBinBlockW + wv * kBinWave + (lane % kBinWave);
-  const uint32_t j = by * kBinBlockH + lane / kBinWave;
-  const uint32_t q = j * (uint32_t)a.Ws + i;
-  int tx0 = 0, ty0 = 0, nx = 0, n = 0;
+  const uint32_t j = by * kBinBlockH + lane / kBinWave, q = j * (uint32_t)a.Ws + i;
+  int tx0 = 0, ty0 = 0, nx = 0, ny = 0;
   unsigned long long key = 0;
   if (i < (uint32_t)a.Ws && j < (uint32_t)a.Hs) {
     const size_t o = (size_t)k * a.ns + q;
@@ -126,69 +124,26 @@ __global__ __launch_bounds__(256) void ewa_bin_kernel(EwaArgs a) {
       tx0 = g.a0 / kEwaTile;
       ty0 = g.b0 / kEwaTile;
       nx = g.a1 / kEwaTile - tx0 + 1;
-      n = nx * (g.b1 / kEwaTile - ty0 + 1);
+      ny = g.b1 / kEwaTile - ty0 + 1;
       key = ((unsigned long long)__float_as_uint(g.z) << 32) | q;
       if (!kFill) {
         const GG_GLOBAL uint8_t *c = gmem(a.rgb) + 3 * o;
-        const float4 r0 = make_float4(g.u, g.v, g.Ah, g.Bn);
-        const float4 r1 = make_float4(g.Ch, unorm8(c[0]), unorm8(c[1]), unorm8(c[2]));
-        *(GG_GLOBAL gg_v4f *)(a.rec + 2 * o) = (gg_v4f){r0.x, r0.y, r0.z, r0.w};
-        *(GG_GLOBAL gg_v4f *)(a.rec + 2 * o + 1) = (gg_v4f){r1.x, r1.y, r1.z, r1.w};
+        *(GG_GLOBAL gg_v4f *)(a.rec + 2 * o) = (gg_v4f){g.u, g.v, g.Ah, g.Bn};
+        *(GG_GLOBAL gg_v4f *)(a.rec + 2 * o + 1) =
+            (gg_v4f){g.Ch, unorm8(c[0]), unorm8(c[1]), unorm8(c[2])};
       }
     }
   }
-  uint32_t *cnt = (kFill ? a.tile_cursor : a.tile_count) + (size_t)k * a.ntiles;
-  // the covered tiles in row-major order: column sx, row sy of the range
-  int sx = 0, sy = 0;
-  for (int s = 0;; ++s) {
-    const bool has = s < n;
-    if (__ballot(has) == 0ull) break;
-    const uint32_t tile = has ? (uint32_t)((ty0 + sy) * a.ntx + (tx0 + sx)) : 0u;
-    if (++sx == nx) {
-      sx = 0;
-      ++sy;
-    }
-    const uint32_t slot = aggregated_slot<kFill>(cnt, tile, has);
-    if (kFill && has) {
-      const uint32_t pos = gmem(a.tile_offset)[(size_t)k * a.ntiles + tile] + slot;
-      if (pos < a.cap) gmem(a.keys)[pos] = key;
-    }
-  }
-}
-
-// A list segment per (view, tile): each wavefront takes an exclusive prefix
-// of its 64 tiles' counts with shuffles and one atomic on the allocator
-// count[n] for its total.  Segments are laid out in atomic order (a tile
-// needs only its own range: offset and count); the fill's cursors are
-// cleared.
-__global__ __launch_bounds__(256) void ewa_alloc_kernel(uint32_t *count, uint32_t *off,
-                                                        uint32_t *cursor, uint32_t n) {
-  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = __lane_id();
-  const uint32_t c = t < n ? gmem(count)[t] : 0u;
-  uint32_t inc = c;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t v = (uint32_t)__shfl_up((int)inc, d);
-    if (lane >= d) inc += v;
-  }
-  const uint32_t total = (uint32_t)__shfl((int)inc, 63);
-  uint32_t base = 0;
-  if (lane == 63 && total) base = gatomic_add(&count[n], total);
-  base = (uint32_t)__shfl((int)base, 63);
-  if (t < n) {
-    gmem(off)[t] = base + inc - c;
-    gmem(cursor)[t] = 0u;
-  }
+  uint32_t *counters = (kFill ? a.tile_cursor : a.tile_count) + (size_t)k * a.ntiles;
+  bin_wave<kFill>(counters, a.ntx, tx0, ty0, nx, ny, [&](uint32_t pos) {
+    if (pos < a.cap) gmem(a.keys)[pos] = key;
+  });
 }
 
 __global__ void ewa_zero_kernel(uint32_t *p, uint32_t n) {
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
     gmem(p)[i] = 0u;
 }
-
-// v_writelane: `old` with lane `lane` set to the wave-uniform `value`.
-extern "C" __device__ int gg_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
 // The raster's cull unit: the tile's pixels in blocks of kEwaBlock x
 // kEwaBlock, each block's lanes walking their own list (2 x 2: sixteen
@@ -536,12 +491,8 @@ int launch_splat_ewa(const EwaArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(ewa_bin_kernel<false>, gsrc, dim3(256), 0, s, a);
     if (int rc = check_hip(hipGetLastError(), "ewa_bin_kernel<count>")) return rc;
   }
-  {
-    KernelTimer t("ewa_alloc", s);
-    hipLaunchKernelGGL(ewa_alloc_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a.tile_count,
-                       a.tile_offset, a.tile_cursor, n);
-    if (int rc = check_hip(hipGetLastError(), "ewa_alloc_kernel")) return rc;
-  }
+  if (int rc = launch_tile_alloc("ewa_alloc", a.tile_count, a.tile_offset, a.tile_cursor, n, s))
+    return rc;
   {
     KernelTimer t("ewa_fill", s);
     hipLaunchKernelGGL(ewa_bin_kernel<true>, gsrc, dim3(256), 0, s, a);

@@ -352,8 +352,8 @@ struct SplatArgs {
   int32_t ntx, nty;     // target tiles per row / column
   uint32_t ntiles;      // per view
   float zmin, rmax2, band;
-  uint32_t *tile_count;   // K x ntiles (+1 for the total)
-  uint32_t *tile_offset;  // K x ntiles + 1
+  uint32_t *tile_count;   // K x ntiles, then the list allocator
+  uint32_t *tile_offset;  // K x ntiles: start of each tile's list segment
   uint32_t *tile_cursor;  // K x ntiles
   uint32_t *list;         // entries: source index
   uint32_t list_cap;
@@ -385,6 +385,10 @@ struct MaskArgs {
 };
 
 int launch_difference_masks(const MaskArgs &a, hipStream_t s);
+// A list segment for each of n counted tiles: its offset, which the fill's cursor starts at;
+// count[n] is the allocator.
+int launch_tile_alloc(const char *what, uint32_t *count, uint32_t *off, uint32_t *cursor,
+                      uint32_t n, hipStream_t s);
 int launch_splat_forward(SplatArgs &a, hipStream_t s);
 int launch_splat_backward(const SplatArgs &a, hipStream_t s);
 

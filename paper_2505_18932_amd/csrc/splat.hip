@@ -6,9 +6,10 @@
 //
 // Pipeline per call (all views at once):
 //   count  - every source pixel computes its target footprint and counts the
-//            16x16 target tiles its candidate window touches (wavefront-
-//            aggregated atomics: lanes hitting the same tile elect a leader);
-//   scan   - exclusive scan of the tile counts (one workgroup);
+//            16x16 target tiles its candidate window touches (one atomic per
+//            wavefront and tile);
+//   scan   - a list segment per tile (prefix sums of 1024 counts, one atomic
+//            each on an allocator; segments in atomic order);
 //   fill   - the same walk writes each source index into its tiles' lists;
 //   raster - one workgroup per (view, tile): z-test as an LDS 64-bit atomic
 //            minimum of (bits(z) << 32 | source index), then the band blend
@@ -25,10 +26,17 @@ __global__ __launch_bounds__(256) void splat_bin_kernel(SplatArgs a) {
   splat_bin_block<kFill>(a, blockIdx.y, blockIdx.x);
 }
 
-__global__ __launch_bounds__(1024) void tile_scan_kernel(const uint32_t *cnt, uint32_t *off,
-                                                         uint32_t *cursor, uint32_t n) {
-  __shared__ ScanLds lds;
-  tile_scan_block(cnt, off, cursor, n, lds);
+__global__ __launch_bounds__(kAllocTiles) void tile_alloc_kernel(uint32_t *count, uint32_t *off,
+                                                                 uint32_t *cursor, uint32_t n) {
+  alloc_block(count, off, cursor, n, blockIdx.x * kAllocTiles);
+}
+
+int launch_tile_alloc(const char *what, uint32_t *count, uint32_t *off, uint32_t *cursor,
+                      uint32_t n, hipStream_t s) {
+  KernelTimer t(what, s);
+  hipLaunchKernelGGL(tile_alloc_kernel, dim3((n + kAllocTiles - 1) / kAllocTiles),
+                     dim3(kAllocTiles), 0, s, count, off, cursor, n);
+  return check_hip(hipGetLastError(), "tile_alloc_kernel");
 }
 
 __global__ void zero_u32_kernel(uint32_t *p, uint32_t n) {
@@ -53,8 +61,8 @@ int launch_splat_forward(SplatArgs &a, hipStream_t s) {
   const dim3 gsrc(splat_bin_blocks((uint32_t)a.Ws, (uint32_t)a.Hs), a.K);
   {
     KernelTimer t("splat_zero", s);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(min((n + 255) / 256, 1024u)), dim3(256), 0, s,
-                       a.tile_count, n);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(min((n + 256) / 256, 1024u)), dim3(256), 0, s,
+                       a.tile_count, n + 1);
     if (int rc = check_hip(hipGetLastError(), "zero_u32_kernel")) return rc;
   }
   {
@@ -62,12 +70,8 @@ int launch_splat_forward(SplatArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(splat_bin_kernel<false>, gsrc, dim3(256), 0, s, a);
     if (int rc = check_hip(hipGetLastError(), "splat_bin_kernel<count>")) return rc;
   }
-  {
-    KernelTimer t("splat_scan", s);
-    hipLaunchKernelGGL(tile_scan_kernel, dim3(1), dim3(1024), 0, s, a.tile_count, a.tile_offset,
-                       a.tile_cursor, n);
-    if (int rc = check_hip(hipGetLastError(), "tile_scan_kernel")) return rc;
-  }
+  if (int rc = launch_tile_alloc("splat_scan", a.tile_count, a.tile_offset, a.tile_cursor, n, s))
+    return rc;
   {
     KernelTimer t("splat_fill", s);
     hipLaunchKernelGGL(splat_bin_kernel<true>, gsrc, dim3(256), 0, s, a);
