@@ -759,6 +759,20 @@ static bool view_in_front(const Proj &P, const gg_camera &tgt, const gg_tsdf_par
   return true;
 }
 
+// The views' rounding bounds, and whether all are in front; false without bounds.  They need bin
+// depths between 0.99 z_near and 1.01 z_far: a bin's 1 / z is rounded by some 2^-22 / z_near, here
+// less than 2^-9 / z_far.
+static bool views_bounded(const Proj *views, int32_t K, const gg_camera &tgt,
+                          const gg_tsdf_params &prm, float (*slack)[3], bool &front) {
+  front = true;
+  if (!(prm.z_far < 8192.0f * prm.z_near)) return false;
+  for (int k = 0; k < K; ++k) {
+    if (!view_slack(views[k], tgt, prm.z_far, slack[k])) return false;
+    front = front && view_in_front(views[k], tgt, prm, slack[k][2]);
+  }
+  return true;
+}
+
 // cells: the cells' depth ranges built with the table, or null.
 static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t K,
                                 const gg_camera &tgt, const gg_tsdf_params &prm, uint32_t band_px,
@@ -788,15 +802,10 @@ static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t 
   a.decay = prm.decay;
   a.cap = prm.weight_cap;
   a.exact_only = fast_reciprocal_safe(a.views, K, tgt, prm.z_far) ? 0 : 1;
-  // The bounds below need bin depths between 0.99 z_near and 1.01 z_far: a bin's 1 / z is
-  // rounded by some 2^-22 / z_near, here less than 2^-9 / z_far.
-  a.test = K > 0 && !a.exact_only && prm.z_far < 8192.0f * prm.z_near;
   a.zfar = prm.z_far * 1.01f;
-  for (int k = 0; k < K && a.test; ++k)
-    a.test = view_slack(a.views[k], tgt, prm.z_far, a.slack[k]) ? 1 : 0;
-  a.front = a.test;
-  for (int k = 0; k < K && a.front; ++k)
-    a.front = view_in_front(a.views[k], tgt, prm, a.slack[k][2]) ? 1 : 0;
+  bool front;
+  a.test = K > 0 && !a.exact_only && views_bounded(a.views, K, tgt, prm, a.slack, front);
+  a.front = a.test && front;
 }
 
 // The cells' place in a workspace of ws_bytes (null if it ends before them).
@@ -984,6 +993,9 @@ int tsdf_raymarch(const gg_camera *src, int32_t K, const float *depth, const gg_
   a.out_acc = out_acc;
   a.out_steps = out_steps;
   a.exact_only = fast_reciprocal_safe(a.views, K, *tgt, prm->z_far) ? 0 : 1;
+  float slack[GG_MAX_VIEWS][3];
+  bool front;
+  a.front = views_bounded(a.views, K, *tgt, *prm, slack, front) && front;
   return launch_raymarch(a, s);
 }
 

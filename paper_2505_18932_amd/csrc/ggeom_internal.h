@@ -292,6 +292,7 @@ struct RaymarchArgs {
   float *out_depth, *out_acc;
   int32_t *out_steps;
   int32_t exact_only;
+  int32_t front;  // 1: every sample is in front of its camera
 };
 
 int launch_raymarch(const RaymarchArgs &a, hipStream_t s);

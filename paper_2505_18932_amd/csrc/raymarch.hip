@@ -17,7 +17,16 @@ struct Fused {
 };
 
 // One view's sample at depth z: its depth Z in the view and its record.
-template <bool kExact>
+// kFrontRows (tsdf_device.h's modes and this one): the host found every
+// sample in front of its camera (Z > 2^-40) and the view's rows short enough
+// for structured loads, whose range check and closing record take the place
+// of the tests of Z, row and column (as in the fusion: a row outside the
+// image reads 0, a column is clamped to the row's closing record, 0).  The
+// march is bound by the vector unit: 1280 x 720 K=4 138 us with the tests, 128
+// without.
+constexpr int kFrontRows = 2;
+
+template <int kMode>
 __device__ __forceinline__ float2 march_sample(const RaymarchArgs &a, int k, float px, float py,
                                                float z, float &Z) {
   const Proj &P = a.views[k];
@@ -26,15 +35,21 @@ __device__ __forceinline__ float2 march_sample(const RaymarchArgs &a, int k, flo
   const float X0 = fmaf(z, h0, P.c[0]);
   const float X1 = fmaf(z, h1, P.c[1]);
   Z = fmaf(z, h2, P.c[2]);
+  const size_t rec = table_view_records(a.Ws, a.Hs);
+  if constexpr (kMode == kFrontRows) {
+    const float inv = recip_rn(Z);
+    const uint32_t i = (uint32_t)floor_i32(X0 * inv), j = (uint32_t)floor_i32(X1 * inv);
+    return rload2(rows_of(a.table + (size_t)k * rec, table_pitch(a.Ws) * 8u, (uint32_t)a.Hs), j,
+                  min(i, (uint32_t)a.Ws) << 3);
+  }
   const float fWs = (float)a.Ws, fHs = (float)a.Hs;
   uint32_t off;
   // recip_rn unless a lane's depth lies in (0, 2^-100] (wave-uniform choice)
   const uint32_t pitch = table_pitch(a.Ws);
-  if (kExact || __any(Z > 0.0f && !(Z > kRecipLo)))
+  if (kMode == kDivide || __any(Z > 0.0f && !(Z > kRecipLo)))
     off = sample_offset<kDivide>(X0, X1, Z, (uint32_t)a.Ws, (uint32_t)a.Hs, pitch, fWs, fHs);
   else
     off = sample_offset<kChecked>(X0, X1, Z, (uint32_t)a.Ws, (uint32_t)a.Hs, pitch, fWs, fHs);
-  const size_t rec = table_view_records(a.Ws, a.Hs);
   return bload2(buffer_of(a.table + (size_t)k * rec, (uint32_t)(rec * 8u)), off);
 }
 
@@ -47,7 +62,7 @@ __device__ __forceinline__ void march_accumulate(float Z, float2 e, float tau, f
   Wo = Wo + w;
 }
 
-template <int KC, bool kExact>
+template <int KC, int kMode>
 __device__ __forceinline__ Fused march_eval(const RaymarchArgs &a, float px, float py, float z,
                                             float tau, float wtmp, float Dp) {
   float S = 0.0f, Wo = 0.0f;
@@ -55,13 +70,13 @@ __device__ __forceinline__ Fused march_eval(const RaymarchArgs &a, float px, flo
     float Z[KC];
     float2 e[KC];
 #pragma unroll
-    for (int k = 0; k < KC; ++k) e[k] = march_sample<kExact>(a, k, px, py, z, Z[k]);
+    for (int k = 0; k < KC; ++k) e[k] = march_sample<kMode>(a, k, px, py, z, Z[k]);
 #pragma unroll
     for (int k = 0; k < KC; ++k) march_accumulate(Z[k], e[k], tau, S, Wo);
   } else {
     for (int k = 0; k < a.K; ++k) {
       float Z;
-      const float2 e = march_sample<kExact>(a, k, px, py, z, Z);
+      const float2 e = march_sample<kMode>(a, k, px, py, z, Z);
       march_accumulate(Z, e, tau, S, Wo);
     }
   }
@@ -80,7 +95,7 @@ __device__ __forceinline__ float march_tau(const RaymarchArgs &a, float z) {
   return a.trunc_in_bins ? (a.trunc * a.du) * (z * z) : a.trunc;
 }
 
-template <int KC, bool kExact>
+template <int KC, int kMode>
 __global__ __launch_bounds__(256) void raymarch_kernel(RaymarchArgs a) {
   const uint32_t pix = blockIdx.x * blockDim.x + threadIdx.x;
   if (pix >= a.npix) return;
@@ -97,7 +112,7 @@ __global__ __launch_bounds__(256) void raymarch_kernel(RaymarchArgs a) {
   int steps = 0;
   while (z <= a.z_far && steps < a.max_samples) {
     const float tau = march_tau(a, z);
-    const Fused f = march_eval<KC, kExact>(a, px, py, z, tau, wtmp, Dp);
+    const Fused f = march_eval<KC, kMode>(a, px, py, z, tau, wtmp, Dp);
     ++steps;
     const float smin = (a.du * z) * z;
     if (f.Wt > 0.0f) {
@@ -122,14 +137,14 @@ __global__ __launch_bounds__(256) void raymarch_kernel(RaymarchArgs a) {
     float lo = zprev, hi = z;
     for (int it = 0; it < 3; ++it) {
       const float mid = lo + (hi - lo) * 0.5f;
-      const Fused f = march_eval<KC, kExact>(a, px, py, mid, march_tau(a, mid), wtmp, Dp);
+      const Fused f = march_eval<KC, kMode>(a, px, py, mid, march_tau(a, mid), wtmp, Dp);
       if (f.Wt > 0.0f && f.S / f.Wt > 0.0f)
         lo = mid;
       else
         hi = mid;
     }
     dep = lo + (hi - lo) * 0.5f;
-    const Fused f = march_eval<KC, kExact>(a, px, py, dep, march_tau(a, dep), wtmp, Dp);
+    const Fused f = march_eval<KC, kMode>(a, px, py, dep, march_tau(a, dep), wtmp, Dp);
     an = wtmp + f.Wo;
   }
   gmem(a.out_depth)[pix] = dep;
@@ -141,9 +156,11 @@ template <int KC>
 static void launch_raymarch_k(const RaymarchArgs &a, hipStream_t s) {
   const dim3 grid((a.npix + 255) / 256);
   if (a.exact_only)
-    hipLaunchKernelGGL((raymarch_kernel<KC, true>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((raymarch_kernel<KC, kDivide>), grid, dim3(256), 0, s, a);
+  else if (a.front && table_rows_ok(a.Ws))
+    hipLaunchKernelGGL((raymarch_kernel<KC, kFrontRows>), grid, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((raymarch_kernel<KC, false>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((raymarch_kernel<KC, kChecked>), grid, dim3(256), 0, s, a);
 }
 
 int launch_raymarch(const RaymarchArgs &a, hipStream_t s) {
