@@ -70,7 +70,7 @@ def measure_copy_gbs(torch, dev, mib=1024, reps=10):
 
 def kernel_sha():
     h = hashlib.sha256()
-    for name in ("tsdf.hip", "tsdf_device.h", "ggeom_internal.h"):
+    for name in ("tsdf.hip", "tsdf_device.h", "fuse_device.h", "ggeom_internal.h"):
         h.update(open(os.path.join(ROOT, "paper_2505_18932_amd", "csrc", name), "rb").read())
     return h.hexdigest()[:16]
 

@@ -1246,6 +1246,23 @@ static bool item_tuned(const gg_batch_item &it) {
   return t.pixels_per_block || t.pixels_per_row || t.bins_per_thread || t.band_width;
 }
 
+// Orders a work list that is grouped by item so that eighth x of it holds eighth x of each item's
+// entries: an XCD then takes a contiguous part of every item, not whole items, whose costs differ
+// by orders of magnitude (measured, 24 items of 640 x 360 to 1920 x 1080: 20.9 ms with
+// whole items, 14.4 spread and with the lists allocated by small workgroups).
+static void spread_items(std::vector<WorkItem> &work) {
+  std::vector<WorkItem> out;
+  out.reserve(work.size());
+  for (size_t x = 0; x < 8; ++x)
+    for (size_t b = 0, e; b < work.size(); b = e) {
+      for (e = b + 1; e < work.size() && work[e].item == work[b].item;) ++e;
+      const size_t n = e - b;
+      out.insert(out.end(), work.begin() + (ptrdiff_t)(b + n * x / 8),
+                 work.begin() + (ptrdiff_t)(b + n * (x + 1) / 8));
+    }
+  work.swap(out);
+}
+
 // Bins per thread of the item's fusion: as its own launch shape gives them
 // (volume_shape), else as the plan's.
 static int item_vec(const gg_batch_item &it, int vec) {
@@ -1368,6 +1385,9 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
   const size_t o_counts = off;
   off += up256(4 * count_words);
   auto put = [&](size_t bytes) { const size_t o = off; off += up256(bytes ? bytes : 1); return o; };
+  // each XCD's part of a list (xcd_tile) takes an eighth of every item
+  for (std::vector<WorkItem> *w : {&conf, &bin, &raster}) spread_items(*w);
+  for (std::vector<WorkItem> &w : integ) spread_items(w);
   const size_t o_conf = put(sizeof(WorkItem) * conf.size()), o_bin = put(sizeof(WorkItem) * bin.size()),
                o_raster = put(sizeof(WorkItem) * raster.size());
   std::vector<size_t> o_integ(groups.size());

@@ -36,7 +36,7 @@ __global__ void batch_bins_kernel(const BatchItem *__restrict__ items) {
 // so the dispatcher balances them as well as a work queue would, and gives
 // the two branches' workgroups their turns as others end (measured, six items
 // of 1280 x 720 to 1920 x 1080 with the binning in persistent workgroups, which
-// kept the fusion's out: 2225 us, 1521 now).  Entries go to the XCDs in
+// kept the fusion's out: 2225 us, 1401 now).  Entries go to the XCDs in
 // contiguous parts (xcd_tile), so the tiles in flight on an XCD are
 // neighbours in the list and share the lines in its L2.
 __global__ __launch_bounds__(256) void batch_conf_kernel(const BatchItem *__restrict__ items,
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void batch_bin_kernel(const BatchItem *__restr
   splat_bin_block<kFill>(items[wi.item].splat, wi.k, work_tile(wi));
 }
 
-__global__ __launch_bounds__(kAllocTiles) void batch_alloc_kernel(
+__global__ __launch_bounds__(kAllocThreads) void batch_alloc_kernel(
     const BatchItem *__restrict__ items, const uint32_t *__restrict__ list) {
   const SplatArgs &a = items[list[blockIdx.x]].splat;
   const uint32_t n = (uint32_t)a.K * a.ntiles;
@@ -111,7 +111,7 @@ int batch_record(BatchPlan &P, hipStream_t s, hipStream_t side, hipEvent_t fork,
   if (P.n_bin) {
     hipLaunchKernelGGL(batch_bin_kernel<false>, dim3(P.n_bin), dim3(256), 0, ss, P.d_items, P.d_bin,
                        P.n_bin);
-    hipLaunchKernelGGL(batch_alloc_kernel, dim3(P.n_splat_items, 16), dim3(kAllocTiles), 0, ss,
+    hipLaunchKernelGGL(batch_alloc_kernel, dim3(P.n_splat_items, 16), dim3(kAllocThreads), 0, ss,
                        P.d_items, P.d_splat_items);
     hipLaunchKernelGGL(batch_bin_kernel<true>, dim3(P.n_bin), dim3(256), 0, ss, P.d_items, P.d_bin,
                        P.n_bin);

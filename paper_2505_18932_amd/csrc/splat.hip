@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void splat_bin_kernel(SplatArgs a) {
   splat_bin_block<kFill>(a, blockIdx.y, blockIdx.x);
 }
 
-__global__ __launch_bounds__(kAllocTiles) void tile_alloc_kernel(uint32_t *count, uint32_t *off,
+__global__ __launch_bounds__(kAllocThreads) void tile_alloc_kernel(uint32_t *count, uint32_t *off,
                                                                  uint32_t *cursor, uint32_t n) {
   alloc_block(count, off, cursor, n, blockIdx.x * kAllocTiles);
 }
@@ -35,7 +35,7 @@ int launch_tile_alloc(const char *what, uint32_t *count, uint32_t *off, uint32_t
                       uint32_t n, hipStream_t s) {
   KernelTimer t(what, s);
   hipLaunchKernelGGL(tile_alloc_kernel, dim3((n + kAllocTiles - 1) / kAllocTiles),
-                     dim3(kAllocTiles), 0, s, count, off, cursor, n);
+                     dim3(kAllocThreads), 0, s, count, off, cursor, n);
   return check_hip(hipGetLastError(), "tile_alloc_kernel");
 }
 

@@ -240,20 +240,27 @@ __device__ __forceinline__ void splat_bin_block(const SplatArgs &a, int k, uint3
 }
 
 // A list segment per tile for the 1024 counters from `base` on, by a
-// workgroup of 1024 threads: an exclusive prefix of their counts and one
+// workgroup of 256 threads (small ones find room beside the other branch of a
+// batch; of 1024 threads they waited 10 ms for it): an exclusive prefix of their counts and one
 // atomic on the allocator count[n] for the total.  Segments are laid out in
 // atomic order (a tile needs only its own range: offset and count); the
 // fill's cursors start at the segments' offsets.  Measured, one workgroup's
 // scan of all counters against this: 14 400 counters 15.9 and 6.7 us, 65 280
 // 51 and 6.5.
-constexpr uint32_t kAllocTiles = 1024;
+constexpr uint32_t kAllocTiles = 1024, kAllocThreads = 256, kAllocPer = kAllocTiles / kAllocThreads;
 
 __device__ __forceinline__ void alloc_block(uint32_t *count, uint32_t *off, uint32_t *cursor,
                                             uint32_t n, uint32_t base) {
-  __shared__ uint32_t wave_total[kAllocTiles / 64], start;
-  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6, i = base + threadIdx.x;
-  const uint32_t c = i < n ? gmem(count)[i] : 0u;
-  uint32_t inc = c;
+  __shared__ uint32_t wave_total[kAllocThreads / 64], start;
+  const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+  const uint32_t i0 = base + threadIdx.x * kAllocPer;
+  uint32_t c[kAllocPer], sum = 0;
+#pragma unroll
+  for (uint32_t v = 0; v < kAllocPer; ++v) {
+    c[v] = i0 + v < n ? gmem(count)[i0 + v] : 0u;
+    sum += c[v];
+  }
+  uint32_t inc = sum;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const uint32_t v = (uint32_t)__shfl_up((int)inc, d);
@@ -264,14 +271,19 @@ __device__ __forceinline__ void alloc_block(uint32_t *count, uint32_t *off, uint
   __syncthreads();
   uint32_t before = 0, total = 0;
 #pragma unroll
-  for (uint32_t w = 0; w < kAllocTiles / 64; ++w) {
+  for (uint32_t w = 0; w < kAllocThreads / 64; ++w) {
     const uint32_t t = wave_total[w];
     before += w < wv ? t : 0u;
     total += t;
   }
   if (threadIdx.x == 0) start = total ? gatomic_add(&count[n], total) : 0u;
   __syncthreads();
-  if (i < n) gmem(off)[i] = gmem(cursor)[i] = start + before + inc - c;
+  uint32_t at = start + before + inc - sum;
+#pragma unroll
+  for (uint32_t v = 0; v < kAllocPer; ++v) {
+    if (i0 + v < n) gmem(off)[i0 + v] = gmem(cursor)[i0 + v] = at;
+    at += c[v];
+  }
 }
 
 constexpr double kFixG = 1099511627776.0;  // 2^40: sums of G and G c
