@@ -389,8 +389,9 @@ int tsdf_integrate(const gg_camera *src, int32_t K, const float *depth, const gg
  * confidence of the supplement), and the bin depths; tsdf_integrate_tabled
  * then fuses from that ws exactly as tsdf_integrate does (bitwise the same
  * outputs).  Arguments as tsdf_integrate; both calls take the same src, K,
- * prm, ws and ws_bytes (gg_workspace_size(GG_OP_TSDF_INTEGRATE, ...)); the
- * caller orders them (one stream, or an event) and keeps ws untouched between. */
+ * prm and ws (gg_workspace_size(GG_OP_TSDF_INTEGRATE, ...), each with or
+ * without its last part); the caller orders them (one stream, or an event)
+ * and keeps ws untouched between. */
 int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
                     const gg_tsdf_params *prm, void *ws, size_t ws_bytes, void *stream);
 int tsdf_integrate_tabled(const gg_camera *src, int32_t K, const gg_camera *tgt,

@@ -808,23 +808,21 @@ static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t 
   a.front = a.test && front;
 }
 
-// The cells' place in a workspace of ws_bytes (null if it ends before them).
+// The cells' place in a workspace of ws_bytes (null if it ends before them).  Whether they hold
+// the table's ranges is for the table to say (closing_record): it may come from another call.
 static uint32_t *cells_of(const TsdfLayout &L, char *w, size_t ws_bytes) {
   return ws_bytes >= L.total ? (uint32_t *)(w + L.cells) : nullptr;
 }
 
 // The view table (per source pixel: usable depth, fusion weight) and the
 // bin depths into the workspace: the part of the fusion that depends on the
-// depth maps only.  ranges: the fusion's view test will read the cells' depth ranges (else they
-// are set to hold every depth, for a later call on the same table).
+// depth maps only.  cells: where to form the depth ranges that the fusion's view test reads, or null.
 static int build_view_table(const gg_camera *src, int32_t K, const float *depth,
                             const gg_tsdf_params *prm, const TsdfLayout &L, char *w,
-                            uint32_t *cells, bool ranges, hipStream_t s) {
+                            uint32_t *cells, hipStream_t s) {
   const int sw = src[0].width, sh = src[0].height;
-  if (int rc = launch_bins(*prm, (float2 *)(w + L.bins), cells, cells ? L.ncells : 0u, ranges, s))
-    return rc;
-  return launch_conf(conf_args(depth, (float2 *)(w + L.table), ranges ? cells : nullptr, sw, sh, K,
-                               prm), s);
+  if (int rc = launch_bins(*prm, (float2 *)(w + L.bins), cells, cells ? L.ncells : 0u, s)) return rc;
+  return launch_conf(conf_args(depth, (float2 *)(w + L.table), cells, sw, sh, K, prm), s);
 }
 
 int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
@@ -835,7 +833,7 @@ int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
   if (!depth) return fail(GG_ERR_INVALID, "%s: NULL array argument", N);
   const TsdfLayout L = tsdf_layout(K, src[0].width, src[0].height, prm->num_bins, false);
   if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
-  return build_view_table(src, K, depth, prm, L, (char *)ws, cells_of(L, (char *)ws, ws_bytes), true,
+  return build_view_table(src, K, depth, prm, L, (char *)ws, cells_of(L, (char *)ws, ws_bytes),
                           (hipStream_t)stream);
 }
 
@@ -877,7 +875,7 @@ static int integrate_impl(const char *N, bool tabled, const gg_camera *src, int3
                       temporal_mask, F_prev, W_prev, F, W, out_depth, out_bin);
   a.test = a.test && fuse_tests(K, a.nblocks, a.front != 0);
   if (!tabled)
-    if (int rc = build_view_table(src, K, depth, prm, L, w, cells, a.test != 0, s)) return rc;
+    if (int rc = build_view_table(src, K, depth, prm, L, w, a.test ? cells : nullptr, s)) return rc;
   return launch_integrate(a, s);
 }
 
@@ -920,7 +918,7 @@ int gg_fusion_stream_probe(const gg_camera *tgt, const gg_tsdf_params *prm,
   if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
   hipStream_t s = (hipStream_t)stream;
   float2 *bins = (float2 *)((char *)ws + L.bins);
-  if (int rc = launch_bins(*prm, bins, nullptr, 0, false, s)) return rc;
+  if (int rc = launch_bins(*prm, bins, nullptr, 0, s)) return rc;
   // the fusion kernel's own launch with no views: every voxel only decays
   // its carried weight (W = min(decay W_prev, cap), F = that weight times
   // F_prev over itself), so the kernel moves exactly its volume stream
@@ -1140,7 +1138,7 @@ int tsdf_integrate_backward(const gg_camera *src, int32_t K, const float *depth,
   char *w = (char *)ws;
   float2 *table = (float2 *)(w + L.table);
   float2 *bins = (float2 *)(w + L.bins);
-  if (int rc = launch_bins(*prm, bins, nullptr, 0, false, s)) return rc;
+  if (int rc = launch_bins(*prm, bins, nullptr, 0, s)) return rc;
   if (int rc = launch_conf(conf_args(depth, table, nullptr, sw, sh, K, prm), s)) return rc;
   TsdfBackArgs a{};
   fill_views(src, K, tgt, a.views);

@@ -28,7 +28,7 @@ __global__ void batch_bins_kernel(const BatchItem *__restrict__ items) {
   for (uint32_t d = threadIdx.x; d < padded_bins(it.D); d += blockDim.x)
     gstore2(it.bins + d, bin_record((int)d, it.D, it.z_near, it.z_far, it.trunc, it.trunc_in_bins));
   for (uint32_t c = threadIdx.x; c < 2 * it.conf.ncells; c += blockDim.x)
-    gmem(it.conf.cells)[c] = cell_start(c, it.conf.ncells, true);
+    gmem(it.conf.cells)[c] = cell_start(c, it.conf.ncells);
 }
 
 // The phases run one workgroup per entry, as their plain launches run one per

@@ -138,12 +138,12 @@ __device__ __forceinline__ FuseView fuse_view(FuseArgs a, int k, float px, float
   return v;
 }
 
-// The record of the sample at pixel (i, j), (0, 0) where that lies outside
-// the image (its zero weight drops it).  kRows: a structured load, row index
+// The record of the sample at pixel (i, j), of weight 0 where that lies
+// outside the image (which drops it).  kRows: a structured load, row index
 // and byte offset in the row; a row outside [0, Hs) -- a negative floor is a
 // huge unsigned row -- is dropped by the load's range check, and a column
-// outside [0, Ws) is clamped to Ws, the row's closing record (0, 0).  Else a
-// range-checked raw load.
+// outside [0, Ws) is clamped to Ws, the row's closing record (weight 0).  Else
+// a range-checked raw load.
 template <bool kRows>
 __device__ __forceinline__ float2 load_record(const FuseView &v, uint32_t i, uint32_t j) {
   if constexpr (kRows) return rload2(v.table, j, min(i, v.Ws) << 3);
@@ -323,7 +323,8 @@ __device__ __forceinline__ void find_live(FuseArgs a, const TileRect &rect, int 
   const float xl = (float)(a->Ws - 1), yl = (float)(a->Hs - 1);
   bool dead = u1 < 0.0f || u0 > xl + 1.0f || v1 < 0.0f || v0 > yl + 1.0f;
   bool free = false;
-  if (a->cells) {
+  // formed with this table (closing_record)?
+  if (a->cells && ((const GG_CONSTANT float *)(const float *)a->table)[2 * a->Ws] != 0.0f) {
     const int a0 = (int)(fminf(fmaxf(u0, 0.0f), xl) * (1.0f / kCell));
     const int a1 = (int)(fminf(fmaxf(u1, 0.0f), xl) * (1.0f / kCell));
     const int c0 = (int)(fminf(fmaxf(v0, 0.0f), yl) * (1.0f / kCell));

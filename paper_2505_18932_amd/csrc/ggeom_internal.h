@@ -96,8 +96,8 @@ __device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, uint32_t off) 
 }
 
 // The view table: per view Hs rows of Ws + 1 records, the last record of each
-// row (0, 0) -- no usable depth, no weight -- so that a sample whose column
-// falls outside the image may read that record instead of being tested.
+// row without weight (closing_record), so that a sample whose column falls
+// outside the image may read that record instead of being tested.
 __host__ __device__ constexpr uint32_t table_pitch(int32_t Ws) { return (uint32_t)Ws + 1u; }
 __host__ __device__ constexpr size_t table_view_records(int32_t Ws, int32_t Hs) {
   return (size_t)Hs * table_pitch(Ws);
@@ -199,7 +199,7 @@ __host__ __device__ constexpr uint32_t cells_across(int32_t n) {
 
 struct ConfArgs {
   const float *depth;  // K x Hs x Ws
-  float2 *table;       // K x Hs x (Ws + 1): (usable depth or +inf, omega), rows closed by (0, 0)
+  float2 *table;       // K x Hs x (Ws + 1): (usable depth or -inf, omega), then closing_record
   // 2 x ncells or null, ncells = K x cells_across(Hs) x cells_across(Ws): per cell the largest,
   // then the least usable depth of the 3 x 3 cells from it (to the right and below), as float
   // bits; set to 0 and +inf beforehand
@@ -321,7 +321,7 @@ int launch_network_inputs(const NetArgs &a, hipStream_t s);
 int launch_blend(const BlendArgs &a, hipStream_t s);
 
 int launch_bins(const gg_tsdf_params &p, float2 *bins, uint32_t *cells, uint32_t ncells,
-                bool ranges, hipStream_t s);
+                hipStream_t s);
 int launch_conf(const ConfArgs &a, hipStream_t s);
 int launch_integrate(const IntegrateArgs &a, hipStream_t s);
 // Which form of the fusion kernel a launch takes (bits of its template arguments).

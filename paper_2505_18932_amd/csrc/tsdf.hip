@@ -17,22 +17,21 @@ namespace gg {
 // depth bins: z_d = 1 / (1/z_near - d du), tau_d = trunc du z_d^2 (in bins)
 
 // (the last bin repeated to a multiple of kFuseBins, so that every chunk of
-// the fusion reads whole), and the start values of the cells' depth ranges or,
-// where no range will be formed, ranges that hold every depth.
+// the fusion reads whole), and the start values of the cells' depth ranges.
 
 __global__ void bins_kernel(int32_t D, float z_near, float z_far, float trunc, int32_t in_bins,
-                            float2 *out, uint32_t *cells, uint32_t ncells, int32_t ranges) {
+                            float2 *out, uint32_t *cells, uint32_t ncells) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 2 * ncells) cells[i] = cell_start(i, ncells, ranges != 0);
+  if (i < 2 * ncells) cells[i] = cell_start(i, ncells);
   if (i < padded_bins(D)) out[i] = bin_record((int)i, D, z_near, z_far, trunc, in_bins);
 }
 
 int launch_bins(const gg_tsdf_params &p, float2 *bins, uint32_t *cells, uint32_t ncells,
-                bool ranges, hipStream_t s) {
+                hipStream_t s) {
   KernelTimer t("bins", s);
   const uint32_t n = 2 * ncells > padded_bins(p.num_bins) ? 2 * ncells : padded_bins(p.num_bins);
   hipLaunchKernelGGL(bins_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p.num_bins,
-                     p.z_near, p.z_far, p.trunc, p.trunc_in_bins, bins, cells, ncells, ranges ? 1 : 0);
+                     p.z_near, p.z_far, p.trunc, p.trunc_in_bins, bins, cells, ncells);
   return check_hip(hipGetLastError(), "bins_kernel");
 }
 

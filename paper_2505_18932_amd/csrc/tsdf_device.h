@@ -180,10 +180,17 @@ __device__ __forceinline__ float row_max(float v) {
   return fmaxf(v, row_swizzle<0x140>(v));  // row mirror
 }
 
-// Start value of word i of ConfArgs::cells: the empty range, for ranges to be formed, or the
-// range of every depth.
-__device__ __forceinline__ uint32_t cell_start(uint32_t i, uint32_t ncells, bool ranges) {
-  return (i < ncells) == ranges ? 0u : 0x7f800000u;
+// Start value of word i of ConfArgs::cells: the empty range.
+__device__ __forceinline__ uint32_t cell_start(uint32_t i, uint32_t ncells) {
+  return i < ncells ? 0u : 0x7f800000u;
+}
+
+// The record that closes each row of a view table: no weight, so its depth changes no sum (0 times
+// a finite clamp) and says whether the cells' ranges were formed with the table.  A fusion may be
+// given a table that another call built without them, and a workspace long enough to hold them:
+// it must not read what nothing wrote.
+__device__ __forceinline__ float2 closing_record(bool ranges) {
+  return make_float2(ranges ? 1.0f : 0.0f, 0.0f);
 }
 
 // The tile's largest and least usable depth into every 3 x 3 window of cells
@@ -243,7 +250,7 @@ __device__ __forceinline__ void conf_tile(const ConfArgs &a, int k, int bx, int 
       dmin = fminf(dmin, dq[r]);
     }
     gstore2(row + i, rec);
-    if (i == a.Ws - 1) gstore2(row + a.Ws, make_float2(0.0f, 0.0f));  // the row's closing record
+    if (i == a.Ws - 1) gstore2(row + a.Ws, closing_record(a.cells != nullptr));
   }
   if (a.cells) cell_range(a, k, i0, j0, dmax, dmin, tile + conf_lds(kRows));
 }
