@@ -97,11 +97,12 @@ def _stream(device, stream):
     return C.c_void_p(s.cuda_stream)
 
 
-def _ws(nbytes, device, ws):
+def _ws(nbytes, device, ws, spare=0):
+    """``ws`` checked (a caller's may lack the last ``spare`` bytes) or a new one of nbytes."""
     if nbytes == 0:
         return None, 0
     if ws is not None:
-        if ws.device != device or ws.numel() * ws.element_size() < nbytes:
+        if ws.device != device or ws.numel() * ws.element_size() < nbytes - spare:
             raise ValueError("workspace too small or on the wrong device")
         return ws, ws.numel() * ws.element_size()
     # torch allocations are 256-byte aligned
@@ -111,6 +112,11 @@ def _ws(nbytes, device, ws):
 def workspace_size(op, K, src_w, src_h, tgt_w, tgt_h, num_bins=2, sp=None) -> int:
     spp = None if sp is None else C.byref(splat_params(sp))
     return int(L.lib().gg_workspace_size(op, K, src_w, src_h, tgt_w, tgt_h, num_bins, spp))
+
+
+def _ranges_bytes(K, src_w, src_h):
+    """The last part of the fusion's workspace, which the calls do without (include/ggeom.h)."""
+    return -(-8 * K * (-(-src_w // 32)) * (-(-src_h // 32)) // 256) * 256
 
 
 def _wh(cams_arr):
@@ -280,7 +286,7 @@ def tsdf_view_table(src, depth, params, *, ws, stream=None):
     sw, sh = _wh(sa)
     _need(depth, torch.float32, (K, sh, sw), "depth", dev)
     need = workspace_size(L.GG_OP_TSDF_INTEGRATE, K, sw, sh, sw, sh, tp.num_bins)
-    wsb, wsn = _ws(need, dev, ws)
+    wsb, wsn = _ws(need, dev, ws, _ranges_bytes(K, sw, sh))
     L.check(L.lib().tsdf_view_table(sa, K, _ptr(depth), C.byref(tp), _ptr(wsb), wsn,
                                     _stream(dev, stream)))
 
@@ -318,7 +324,7 @@ def tsdf_integrate(src, depth, tgt, params, *, F_prev=None, W_prev=None, F=None,
     need = workspace_size(L.GG_OP_TSDF_INTEGRATE, K, sw, sh, tw, th, D)
     if table_ready and ws is None:
         raise ValueError("table_ready needs the workspace tsdf_view_table filled")
-    wsb, wsn = _ws(need, dev, ws)
+    wsb, wsn = _ws(need, dev, ws, _ranges_bytes(K, sw, sh))
     if table_ready:
         L.check(L.lib().tsdf_integrate_tabled(sa, K, C.byref(tg), C.byref(tp), _ptr(mask),
                                               _ptr(F_prev), _ptr(W_prev), _ptr(F), _ptr(W),
@@ -344,7 +350,7 @@ def fusion_stream_probe(tgt, params, F_prev, W_prev, F, W, out_depth, out_bin, *
     _need(out_depth, torch.float32, vol[:2], "out_depth", dev)
     _need(out_bin, torch.int32, vol[:2], "out_bin", dev)
     need = workspace_size(L.GG_OP_TSDF_INTEGRATE, 1, 1, 1, tg.width, tg.height, tp.num_bins)
-    wsb, wsn = _ws(need, dev, ws)
+    wsb, wsn = _ws(need, dev, ws, _ranges_bytes(1, 1, 1))
     L.check(L.lib().gg_fusion_stream_probe(C.byref(tg), C.byref(tp), _ptr(F_prev), _ptr(W_prev),
                                            _ptr(F), _ptr(W), _ptr(out_depth), _ptr(out_bin),
                                            _tref(tuning), _ptr(wsb), wsn, _stream(dev, stream)))
@@ -405,7 +411,7 @@ def tsdf_raymarch(src, depth, tgt, params, *, depth_prev=None, acc_prev=None, ma
         _need(out_acc, torch.float32, (th, tw), "out_acc", dev)
     st = torch.empty((th, tw), dtype=torch.int32, device=dev) if steps else None
     need = workspace_size(L.GG_OP_TSDF_INTEGRATE, K, sw, sh, tw, th, tp.num_bins)
-    wsb, wsn = _ws(need, dev, ws)
+    wsb, wsn = _ws(need, dev, ws, _ranges_bytes(K, sw, sh))
     L.check(L.lib().tsdf_raymarch(sa, K, _ptr(depth), C.byref(tg), C.byref(tp), _ptr(depth_prev),
                                   _ptr(acc_prev), _ptr(mask), _ptr(od), _ptr(oa), _ptr(st),
                                   _ptr(wsb), wsn, _stream(dev, stream)))

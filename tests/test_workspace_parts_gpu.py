@@ -56,3 +56,40 @@ def test_table_without_ranges_in_a_workspace_with_them(w, h, k, ring, bins, fill
     torch.cuda.synchronize()
     for g, r, what in zip(out, ref, ("F", "W", "depth", "bin")):
         assert np.array_equal(bits(g), bits(r)), what
+
+
+def test_python_calls_take_a_workspace_without_its_last_part():
+    """Every call that takes the fusion's workspace takes one of the bytes it needs, and refuses
+    one byte less."""
+    w, h, k, bins = 130, 70, 3, 20
+    c = scenes.small_ring(seed=8, width=w, height=h, k=k, n_ring=16, bins=bins, noise=0.01, holes=0.03)
+    src, tgt, prm = c["src"], c["tgt"], c["tsdf"]
+    depth = torch.from_numpy(c["depth"]).cuda()
+    base = parts(k, w, h, bins)[0]
+    ref = gg.tsdf_integrate(src, depth, tgt, prm)
+    march = gg.tsdf_raymarch(src, depth, tgt, prm, steps=True)
+    ws = torch.empty(base, dtype=torch.uint8, device="cuda")
+    full = torch.empty(parts(k, w, h, bins)[1], dtype=torch.uint8, device="cuda")
+    gg.tsdf_view_table(src, depth, prm, ws=full[:base])
+    got = [gg.tsdf_integrate(src, depth, tgt, prm, ws=full, table_ready=True)]
+    gg.tsdf_view_table(src, depth, prm, ws=ws)
+    got += [gg.tsdf_integrate(src, depth, tgt, prm, ws=ws, table_ready=True),
+            gg.tsdf_integrate(src, depth, tgt, prm, ws=ws)]
+    for g in got:
+        for a, r in zip(g, ref):
+            assert np.array_equal(bits(a), bits(r))
+    for a, r in zip(gg.tsdf_raymarch(src, depth, tgt, prm, steps=True, ws=ws), march):
+        assert np.array_equal(bits(a), bits(r))
+    F, W = ref[0].clone(), ref[1].clone()
+    probe = dict(tgt=tgt, params=prm, F_prev=F, W_prev=W, F=F, W=W, out_depth=ref[2].clone(),
+                 out_bin=ref[3].clone())
+    ops.fusion_stream_probe(**probe, ws=ws[:parts(1, 1, 1, bins)[0]])
+    torch.cuda.synchronize()
+    for call in (lambda x: gg.tsdf_view_table(src, depth, prm, ws=x),
+                 lambda x: gg.tsdf_integrate(src, depth, tgt, prm, ws=x),
+                 lambda x: gg.tsdf_integrate(src, depth, tgt, prm, ws=x, table_ready=True),
+                 lambda x: gg.tsdf_raymarch(src, depth, tgt, prm, ws=x)):
+        with pytest.raises(ValueError):
+            call(ws[:base - 1])
+    with pytest.raises(ValueError):
+        ops.fusion_stream_probe(**probe, ws=ws[:parts(1, 1, 1, bins)[0] - 1])
