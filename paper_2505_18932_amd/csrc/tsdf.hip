@@ -121,21 +121,33 @@ int launch_integrate(const IntegrateArgs &a, hipStream_t s) {
 // D=128 166 and 94 (F alone: 91 at the copy's rate), 333 x 200 D=100 13.8 and
 // 11.7.
 
-template <uint32_t kWide>
+template <uint32_t kWide, int kAux = 0>
 __device__ __forceinline__ void bload(__amdgpu_buffer_rsrc_t r, uint32_t off, float (&o)[kWide]) {
   if constexpr (kWide == 4) {
-    const gg_v4f v = __builtin_bit_cast(gg_v4f, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    const gg_v4f v = __builtin_bit_cast(gg_v4f, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kAux));
     o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
+  } else if constexpr (kWide == 2) {
+    const gg_v2f v = __builtin_bit_cast(gg_v2f, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kAux));
+    o[0] = v.x; o[1] = v.y;
   } else {
-    o[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    o[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kAux));
   }
 }
 
-// kWide: floats per lane and load, 4 (D a multiple of 4, the volume 16-byte aligned) or 1.
-template <uint32_t kWide, uint32_t kPixels, uint32_t kLines>
+// kWide: floats per lane and load, 4 or 2 (D a multiple, the volume aligned to them) or 1.
+// kLanes: lanes of a group, 32 / kWide (a line) or, where they hold all D bins, fewer.
+// kW: when W is loaded.
+enum : int {
+  kWhereNeeded,  // where F changes sign: a second trip to memory, but few lines
+  kWithF,        // the group holds all D bins, a fraction of a line or one: the trip costs more
+  kStreamed,     // with F, both non-temporal
+};
+template <uint32_t kWide, uint32_t kLanes, uint32_t kPixels, uint32_t kLines, int kW>
 __global__ __launch_bounds__(256) void extract_kernel(ExtractArgs a) {
-  constexpr uint32_t kLanes = 32 / kWide, kGroups = 64 / kLanes;
+  constexpr uint32_t kGroups = 64 / kLanes, kLine = kLanes * kWide;
   constexpr uint64_t kGroup = (1ull << kLanes) - 1;
+  constexpr bool kBoth = kW != kWhereNeeded;
+  constexpr int kAux = kW == kStreamed ? 2 : 0;
   const uint32_t lane = threadIdx.x & 63u, group = lane / kLanes, sub = lane % kLanes;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t p0 = (xcd_tile(blockIdx.x, gridDim.x) * 4u + wave) * (kGroups * kPixels);
@@ -143,22 +155,25 @@ __global__ __launch_bounds__(256) void extract_kernel(ExtractArgs a) {
   const uint32_t D = (uint32_t)a.D, np = min(a.npix - p0, kGroups * kPixels);
   const auto F = buffer_of(a.F + (size_t)p0 * D, np * D * 4u);
   const auto W = buffer_of(a.W + (size_t)p0 * D, np * D * 4u);
-  float prev[kPixels];  // F of the bin before the lines
+  float prev[kPixels], prevw[kPixels];  // F and W of the bin before the lines
   bool done[kPixels];
 #pragma unroll
   for (uint32_t p = 0; p < kPixels; ++p) {
-    prev[p] = 0.0f;
+    prev[p] = prevw[p] = 0.0f;
     done[p] = p * kGroups + group >= np;
   }
-  for (uint32_t d0 = 0; d0 < D; d0 += 32u * kLines) {
+  for (uint32_t d0 = 0; d0 < D; d0 += kLine * kLines) {
     float f[kPixels][kLines][kWide], left[kPixels][kLines];
+    float w[kPixels][kLines][kWide], wl[kPixels][kLines][1];
 #pragma unroll
     for (uint32_t p = 0; p < kPixels; ++p)
 #pragma unroll
       for (uint32_t l = 0; l < kLines; ++l) {
-        const uint32_t d = d0 + 32u * l + sub * kWide;
-        bload<kWide>(F, !done[p] && d < D ? ((p * kGroups + group) * D + d) * 4u : kOutOfRange,
-                     f[p][l]);
+        const uint32_t d = d0 + kLine * l + sub * kWide;
+        const uint32_t off =
+            !done[p] && d < D ? ((p * kGroups + group) * D + d) * 4u : kOutOfRange;
+        bload<kWide, kAux>(F, off, f[p][l]);
+        if constexpr (kBoth) bload<kWide, kAux>(W, off, w[p][l]);
       }
     // crossings of F between bins d - 1 and d: F of the first, and whether there is one
     bool cross[kPixels][kLines], any = false;
@@ -166,10 +181,15 @@ __global__ __launch_bounds__(256) void extract_kernel(ExtractArgs a) {
     for (uint32_t p = 0; p < kPixels; ++p)
 #pragma unroll
       for (uint32_t l = 0; l < kLines; ++l) {
-        const uint32_t d = d0 + 32u * l + sub * kWide;
+        const uint32_t d = d0 + kLine * l + sub * kWide;
         const float up = __shfl_up(f[p][l][kWide - 1], 1, kLanes);
         left[p][l] = sub == 0 ? prev[p] : up;
         prev[p] = __shfl(f[p][l][kWide - 1], kLanes - 1, kLanes);
+        if constexpr (kBoth) {
+          const float upw = __shfl_up(w[p][l][kWide - 1], 1, kLanes);
+          wl[p][l][0] = sub == 0 ? prevw[p] : upw;
+          prevw[p] = __shfl(w[p][l][kWide - 1], kLanes - 1, kLanes);
+        }
         bool c = false;
 #pragma unroll
         for (uint32_t v = 0; v < kWide; ++v)
@@ -179,16 +199,17 @@ __global__ __launch_bounds__(256) void extract_kernel(ExtractArgs a) {
       }
     if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
     // both bins observed?
-    float w[kPixels][kLines][kWide], wl[kPixels][kLines][1];
+    if constexpr (!kBoth) {
 #pragma unroll
-    for (uint32_t p = 0; p < kPixels; ++p)
+      for (uint32_t p = 0; p < kPixels; ++p)
 #pragma unroll
-      for (uint32_t l = 0; l < kLines; ++l) {
-        const uint32_t d = d0 + 32u * l + sub * kWide;
-        const uint32_t off = ((p * kGroups + group) * D + d) * 4u;
-        bload<kWide>(W, cross[p][l] ? off : kOutOfRange, w[p][l]);
-        bload<1>(W, cross[p][l] && d ? off - 4u : kOutOfRange, wl[p][l]);
-      }
+        for (uint32_t l = 0; l < kLines; ++l) {
+          const uint32_t d = d0 + kLine * l + sub * kWide;
+          const uint32_t off = ((p * kGroups + group) * D + d) * 4u;
+          bload<kWide>(W, cross[p][l] ? off : kOutOfRange, w[p][l]);
+          bload<1>(W, cross[p][l] && d ? off - 4u : kOutOfRange, wl[p][l]);
+        }
+    }
     bool all = true;
 #pragma unroll
     for (uint32_t p = 0; p < kPixels; ++p) {
@@ -201,7 +222,7 @@ __global__ __launch_bounds__(256) void extract_kernel(ExtractArgs a) {
           const float g0 = v ? f[p][l][v ? v - 1 : 0] : left[p][l];
           const float w0 = v ? w[p][l][v ? v - 1 : 0] : wl[p][l][0];
           if (g0 > 0.0f && f[p][l][v] <= 0.0f && w0 > 0.0f && w[p][l][v] > 0.0f) {
-            best = (int)(d0 + 32u * l + sub * kWide) + v - 1;
+            best = (int)(d0 + kLine * l + sub * kWide) + v - 1;
             f0 = g0;
             f1 = f[p][l][v];
           }
@@ -230,24 +251,53 @@ __global__ __launch_bounds__(256) void extract_kernel(ExtractArgs a) {
     }
 }
 
-template <uint32_t kWide, uint32_t kPixels, uint32_t kLines>
+template <uint32_t kWide, uint32_t kLanes, uint32_t kPixels, uint32_t kLines, int kW>
 static void launch_extract_form(const ExtractArgs &a, hipStream_t s) {
-  const uint32_t per = 4u * (64u * kWide / 32u) * kPixels;
-  hipLaunchKernelGGL((extract_kernel<kWide, kPixels, kLines>), dim3((a.npix + per - 1) / per),
-                     dim3(256), 0, s, a);
+  const uint32_t per = 4u * (64u / kLanes) * kPixels;
+  hipLaunchKernelGGL((extract_kernel<kWide, kLanes, kPixels, kLines, kW>),
+                     dim3((a.npix + per - 1) / per), dim3(256), 0, s, a);
 }
 
+// Few bins: the fewest lanes, a power of two, that hold them.
+template <uint32_t kWide, uint32_t kPixels, uint32_t kLanes>
+static void launch_extract_few(const ExtractArgs &a, hipStream_t s) {
+  constexpr uint32_t kHalf = kLanes / 2;
+  if constexpr (kHalf * kWide >= 2)
+    if ((uint32_t)a.D <= kHalf * kWide) return launch_extract_few<kWide, kPixels, kHalf>(a, s);
+  launch_extract_form<kWide, kLanes, kPixels, 1, kWithF>(a, s);
+}
+
+// Up to 16 bins (32 by vector loads), groups of as many lanes as hold them (measured, whole lines
+// of 8 or 32 lanes as for more bins, and this: 1280 x 720 D=3 58 and 11.1 us, D=4 22.7 and 6.6, D=8
+// 24.0 and 12.6, D=14 60 and 22, D=24 33.4 and 28.9; 333 x 200 D=4 4.6 and 3.2), streamed where F
+// and W exceed the 256 MB cache (1920 x 1080 D=24: 75 us, 67 streamed; 1280 x 720 D=24: 29.1 and
+// 30.5).  Of more bins, small volumes take two or four lines at once (one line and this: 160 x 100
+// D=48 4.7 and 3.9 us, D=255 11.7 and 7.0, 333 x 200 D=100 12.2 and 11.7; but 420 x 260 D=48 10.3
+// and 12.7, 512 x 288 D=96 19.3 and 21.5, 1280 x 720 D=128 95 and 117).
 int launch_extract(const ExtractArgs &a, hipStream_t s) {
   KernelTimer t("extract", s);
-  const bool vec = a.D % 4 == 0 && (((uintptr_t)a.F | (uintptr_t)a.W) & 15u) == 0;
-  // Measured, one line and four at a time: 160 x 100 D=255 11.7 and 9.6 us, 333 x 200 D=100 12.2
-  // and 11.7; 420 x 260 D=48 10.3 and 12.7, 512 x 288 D=96 19.3 and 21.5, 1280 x 720 D=128 95 and
-  // 117.
-  const bool small = a.D > 64 && (size_t)a.npix * (size_t)a.D <= (size_t)8 << 20;
-  if (vec)
-    small ? launch_extract_form<4, 1, 4>(a, s) : launch_extract_form<4, 2, 1>(a, s);
+  const uintptr_t base = (uintptr_t)a.F | (uintptr_t)a.W;
+  const bool vec = a.D % 4 == 0 && (base & 15u) == 0, vec2 = a.D % 2 == 0 && (base & 7u) == 0;
+  const size_t voxels = (size_t)a.npix * (size_t)a.D;
+  if (vec && a.D <= 16)
+    launch_extract_few<4, 1, 4>(a, s);
+  else if (vec && a.D <= 32)
+    voxels > (size_t)32 << 20 ? launch_extract_form<4, 8, 2, 1, kStreamed>(a, s)
+    : a.npix > 1u << 17       ? launch_extract_form<4, 8, 2, 1, kWithF>(a, s)
+                              : launch_extract_form<4, 8, 1, 1, kWithF>(a, s);
+  else if (vec2 && a.D <= 32)
+    launch_extract_few<2, 2, 16>(a, s);
+  else if (a.D <= 16)
+    a.npix > 1u << 17 ? launch_extract_few<1, 4, 16>(a, s) : launch_extract_few<1, 2, 16>(a, s);
+  else if (a.D > 64 && voxels <= (size_t)8 << 20)
+    vec ? launch_extract_form<4, 8, 1, 4, kWhereNeeded>(a, s)
+        : launch_extract_form<1, 32, 2, 4, kWhereNeeded>(a, s);
+  else if (a.D > 32 && voxels <= (size_t)1 << 20)
+    vec ? launch_extract_form<4, 8, 1, 2, kWhereNeeded>(a, s)
+        : launch_extract_form<1, 32, 2, 2, kWhereNeeded>(a, s);
   else
-    small ? launch_extract_form<1, 2, 4>(a, s) : launch_extract_form<1, 4, 1>(a, s);
+    vec ? launch_extract_form<4, 8, 2, 1, kWhereNeeded>(a, s)
+        : launch_extract_form<1, 32, 4, 1, kWhereNeeded>(a, s);
   return check_hip(hipGetLastError(), "extract_kernel");
 }
 
