@@ -694,6 +694,27 @@ static int fill_views(const gg_camera *src, int32_t K, const gg_camera *tgt, Pro
   return GG_OK;
 }
 
+// The depths at which a call samples: its bins' (the FP32 operations of bin_depth: z_d rises with
+// d, as each of them is monotone) and the march's, from z_near to z_far.  ok: all are positive and
+// finite.  Where z_far exceeds z_near by some 2^24 bins the last bin's 1 / z can round to 0 or less.
+struct DepthRange {
+  float lo, hi;
+  bool ok;
+};
+
+static DepthRange depth_range(const gg_tsdf_params &p) {
+  const float un = 1.0f / p.z_near, uf = 1.0f / p.z_far;
+  const float du = (un - uf) / (float)(p.num_bins - 1);
+  const float u = un - (float)(p.num_bins - 1) * du;
+  const float first = 1.0f / un, last = 1.0f / u;
+  DepthRange r{p.z_near, p.z_far, u > 0.0f && std::isfinite(first) && std::isfinite(last)};
+  if (r.ok) {
+    r.lo = std::min(r.lo, first);
+    r.hi = std::max(r.hi, last);
+  }
+  return r;
+}
+
 // True when every sample's view depth z_k = z h2 + c2 (z <= z_far, pixel
 // centres inside the target) stays below 2^99, where the kernels' fast
 // reciprocal is exact; otherwise they take IEEE division throughout.
@@ -748,10 +769,10 @@ static bool view_slack(const Proj &P, const gg_camera &tgt, float z_far, float *
 
 // True where every sample of the view has Z > 2^-40, in which the kernels' arithmetic keeps to
 // its fast form: Z is bilinear in the pixel and the depth, so its least is at a corner.
-static bool view_in_front(const Proj &P, const gg_camera &tgt, const gg_tsdf_params &prm,
+static bool view_in_front(const Proj &P, const gg_camera &tgt, const DepthRange &range,
                           double slack) {
   for (int c = 0; c < 8; ++c) {
-    const double z = (c & 4) ? prm.z_far * 1.01 : prm.z_near * 0.99;
+    const double z = (c & 4) ? range.hi * 1.01 : range.lo * 0.99;
     const double h2 = (double)P.H[6] * ((c & 1) ? tgt.width : 0) +
                       (double)P.H[7] * ((c & 2) ? tgt.height : 0) + (double)P.H[8];
     if (!(z * h2 + (double)P.c[2] - slack > std::ldexp(1.0, -40))) return false;
@@ -759,16 +780,14 @@ static bool view_in_front(const Proj &P, const gg_camera &tgt, const gg_tsdf_par
   return true;
 }
 
-// The views' rounding bounds, and whether all are in front; false without bounds.  They need bin
-// depths between 0.99 z_near and 1.01 z_far: a bin's 1 / z is rounded by some 2^-22 / z_near, here
-// less than 2^-9 / z_far.
+// The views' rounding bounds, and whether all are in front; false without bounds.
 static bool views_bounded(const Proj *views, int32_t K, const gg_camera &tgt,
-                          const gg_tsdf_params &prm, float (*slack)[3], bool &front) {
+                          const DepthRange &range, float (*slack)[3], bool &front) {
   front = true;
-  if (!(prm.z_far < 8192.0f * prm.z_near)) return false;
+  if (!range.ok) return false;
   for (int k = 0; k < K; ++k) {
-    if (!view_slack(views[k], tgt, prm.z_far, slack[k])) return false;
-    front = front && view_in_front(views[k], tgt, prm, slack[k][2]);
+    if (!view_slack(views[k], tgt, range.hi, slack[k])) return false;
+    front = front && view_in_front(views[k], tgt, range, slack[k][2]);
   }
   return true;
 }
@@ -801,10 +820,11 @@ static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t 
   set_band_order(a, tgt.width, tgt.height, band_px);
   a.decay = prm.decay;
   a.cap = prm.weight_cap;
-  a.exact_only = fast_reciprocal_safe(a.views, K, tgt, prm.z_far) ? 0 : 1;
-  a.zfar = prm.z_far * 1.01f;
+  const DepthRange range = depth_range(prm);
+  a.exact_only = fast_reciprocal_safe(a.views, K, tgt, range.hi) ? 0 : 1;
+  a.zfar = range.hi * 1.01f;
   bool front;
-  a.test = K > 0 && !a.exact_only && views_bounded(a.views, K, tgt, prm, a.slack, front);
+  a.test = K > 0 && !a.exact_only && views_bounded(a.views, K, tgt, range, a.slack, front);
   a.front = a.test && front;
 }
 
@@ -990,10 +1010,11 @@ int tsdf_raymarch(const gg_camera *src, int32_t K, const float *depth, const gg_
   a.out_depth = out_depth;
   a.out_acc = out_acc;
   a.out_steps = out_steps;
-  a.exact_only = fast_reciprocal_safe(a.views, K, *tgt, prm->z_far) ? 0 : 1;
+  const DepthRange range = depth_range(*prm);
+  a.exact_only = fast_reciprocal_safe(a.views, K, *tgt, range.hi) ? 0 : 1;
   float slack[GG_MAX_VIEWS][3];
   bool front;
-  a.front = views_bounded(a.views, K, *tgt, *prm, slack, front) && front;
+  a.front = views_bounded(a.views, K, *tgt, range, slack, front) && front;
   return launch_raymarch(a, s);
 }
 
