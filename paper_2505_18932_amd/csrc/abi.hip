@@ -1385,7 +1385,10 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
     IntegrateArgs probe{};  // the item's form and tile order
     make_integrate_args(probe, it.src, it.K, it.tgt, it.tsdf, band_pixels(&it.volume), nullptr,
                         nullptr, nullptr, nullptr, it.F_prev, it.W_prev, it.F, it.W, nullptr, nullptr);
-    const int form = integrate_form(probe), waves = fuse_waves(D, 1u << 20, form_direct(form));
+    // (the batch's tiles run together: no launch is small)
+    const int form = integrate_form(probe);
+    const FuseShape shape = fuse_shape(form, K, D, UINT32_MAX);
+    const int waves = shape.waves;
     size_t gi = 0;
     while (gi < groups.size() && !(groups[gi].form == form && groups[gi].waves == waves)) ++gi;
     if (gi == groups.size()) {
@@ -1395,6 +1398,7 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
       groups.push_back(g);
       integ.emplace_back();
     }
+    groups[gi].lds = std::max(groups[gi].lds, shape.lds);
     // the item's tiles in the plain launch's visiting order (bands)
     for (uint32_t s = 0; s < probe.nblocks; ++s) {
       const uint32_t t = band_tile(probe, s);
@@ -1434,7 +1438,9 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
     make_integrate_args(d.integ, it.src, it.K, it.tgt, it.tsdf, band_pixels(&it.volume), table,
                         bins, (const float *)cells, it.temporal_mask, it.F_prev, it.W_prev, it.F,
                         it.W, it.out_depth, it.out_bin);
-    // (the batch's tiles run together: no launch is small)
+    const FuseShape shape = fuse_shape(integrate_form(d.integ), it.K, d.integ.D, UINT32_MAX);
+    d.integ.row = shape.row;
+    d.integ.span = shape.span;
     d.integ.test = d.integ.test && fuse_tests(it.K, UINT32_MAX, d.integ.front != 0);
     if (it.rgb) {
       make_splat_args(d.splat, it.src, it.K, it.depth, it.rgb, it.tgt, it.splat, sl[i],

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void batch_raster_kernel(const BatchItem *__re
 // launch in the same form of the plain kernel (so the same code); each
 // item's tiles are listed in the plain launch's band order.
 template <int kForm>
-__global__ __launch_bounds__(64 * kFuseMaxWaves) void batch_integrate_kernel(
+__global__ __launch_bounds__(64 * kFuseMaxWaves, form_waves(kForm)) void batch_integrate_kernel(
     const BatchItem *__restrict__ items, const WorkItem *__restrict__ work, uint32_t n) {
   extern __shared__ __align__(16) float smem[];
   const WorkItem wi = uniform_entry(work, xcd_tile(blockIdx.x, n));
@@ -88,7 +88,7 @@ static void launch_integ_form(const BatchPlan &P, const IntegGroup &g, hipStream
     if (g.form != kForm) return launch_integ_form<kForm + 1>(P, g, s);
     if constexpr (form_exists(kForm))
       hipLaunchKernelGGL(batch_integrate_kernel<kForm>, dim3(g.n), dim3(64 * g.waves),
-                         FuseLds::bytes(g.waves), s, P.d_items, g.list, g.n);
+                         g.lds, s, P.d_items, g.list, g.n);
   }
 }
 

@@ -54,6 +54,7 @@ __device__ __forceinline__ uint32_t work_tile(const WorkItem &w) {
 // workgroup size.
 struct IntegGroup {
   int form = 0, waves = 0;
+  size_t lds = 0;              // the largest of its items'
   WorkItem *list = nullptr;    // device
   uint32_t n = 0;
 };

@@ -11,7 +11,8 @@
 // image, which one test (find_live) can find to hold nothing to keep, or to
 // lie in free space.  The volume moves in the other layout: the workgroup
 // streams each pixel's run of the slab's bins (whole 128-byte lines with four
-// wavefronts where D allows), and LDS exchanges the two.
+// wavefronts where D allows), and LDS exchanges the two.  Volumes written
+// without a carry whose bins make no whole lines go by integrate_windows.
 #pragma once
 
 #include <type_traits>
@@ -21,7 +22,7 @@
 namespace gg {
 
 constexpr int kFuseBins = 8;        // per lane and slab
-constexpr int kFuseMaxWaves = 16;   // of a workgroup (LDS: 79 KB)
+constexpr int kFuseMaxWaves = 16;   // of a workgroup (LDS of slabs: 79 KB)
 
 // Wavefronts per workgroup for D bins and a launch of nblocks workgroups:
 // four, where a slab is one 128-byte line of each pixel if D is a multiple of
@@ -76,13 +77,64 @@ enum : int {
   kFormLines = 2,  // and slabs of whole lines; a carried volume is loaded straight into LDS
   kFormRows = 4,   // structured view-table loads
   kFormCarry = 8,  // the previous volume is carried
-  kFuseForms = 16
+  kFormWindows = 16,  // neither carry nor whole lines: integrate_windows
+  kFuseForms = 32
 };
 __host__ __device__ constexpr bool form_exists(int f) {
-  return (f & kFormVec) || !(f & kFormLines);
+  if (f & kFormWindows) return !(f & (kFormCarry | kFormLines));
+  return (f & kFormVec) || ((f & kFormCarry) && !(f & kFormLines));
 }
 __host__ __device__ constexpr bool form_direct(int f) {
   return (f & kFormLines) && (f & kFormCarry);
+}
+// Wavefronts per SIMD that the registers must leave room for: three workgroups of eight.
+__host__ __device__ constexpr int form_waves(int f) { return f & kFormWindows ? 6 : 4; }
+
+// The bins of which one window holds a whole row in LDS, and of which two workgroups still fit a
+// compute unit.
+constexpr int kFuseWhole = 312, kFuseWholeTwice = 156;
+
+// Whether a launch without a carry, whose bins are not whole lines, goes by windows instead of
+// slabs (integrate_windows).  Measured, slabs and windows: 1920 x 1080 K=1 D=100 831 and 351 us,
+// K=8 D=75 1389 and 865; 1280 x 720 K=4 D=200 815 and 568; 637 x 359 K=6 D=104 131 and 118.  But
+// with more bins than two workgroups have room for, few views and a volume that the 256 MB cache
+// absorbs: 637 x 359 D=164 K=1 80 and 103, K=2 95 and 111.
+__host__ __device__ constexpr bool fuse_windows(int K, int D, bool vec, size_t npix) {
+  return !(vec && D > kFuseWholeTwice && K <= 3 && npix * (size_t)D <= (size_t)40 << 20);
+}
+
+// A launch's workgroups: wavefronts and LDS; of windows also their bins and LDS row.
+struct FuseShape {
+  int waves, span;
+  uint32_t row;
+  size_t lds;
+};
+
+// Windows of all bins where LDS holds them, the wavefronts taking their chunks in two rounds up to
+// 64 bins, then eight or twelve of them (measured, 1280 x 720 K=1: D=48 with 3, 4 and 8 96, 101 and
+// 117 us; D=100 with 7, 8, 12 and 13 180, 169, 187 and 266; D=125 with 8, 12 and 16 239, 225 and
+// 320).  More than 156 bins leave one workgroup per compute unit: vector accesses of two or more
+// views then take windows of 64 bins, three workgroups (1280 x 720 D=200 K=4 734 and 566, K=2 580
+// and 461; K=1 446 and 452; single floats of D=233 K=4 821 and 1065: one window).
+__host__ inline FuseShape fuse_shape(int form, int K, int D, uint32_t nblocks) {
+  FuseShape s{fuse_waves(D, nblocks, form_direct(form)), 0, 0u, 0};
+  s.lds = FuseLds::bytes(s.waves);
+  if (form & kFormWindows) {
+    const int chunks = (D + kFuseBins - 1) / kFuseBins;
+    const bool more = D > kFuseWholeTwice;
+    if (nblocks > 512) {
+      const int rounds = (chunks + kFuseMaxWaves - 1) / kFuseMaxWaves;
+      s.waves = D > 64 && D <= 108 ? 8 : D > 64 && !more ? 12 : (chunks - 1) / (rounds > 2 ? rounds : 2) + 1;
+    }
+    s.span = kFuseBins * chunks;
+    if (D > kFuseWhole || (more && K > 1 && nblocks > 512 && (form & kFormVec))) {
+      s.waves = 8;
+      s.span = 64;
+    }
+    s.row = (uint32_t)(s.span < D ? s.span + 36 : D);  // a ring's padded against bank conflicts
+    s.lds = sizeof(float) * (2 * kFusePix * s.row + 2 * kFusePix);
+  }
+  return s;
 }
 
 // Read-only data addressed with wave-uniform addresses through the scalar
@@ -511,9 +563,226 @@ __device__ __forceinline__ unsigned long long crossing_key(int d, float za, floa
   return ((unsigned long long)(uint32_t)d << 32) | __float_as_uint(za + (zb - za) * frac);
 }
 
+// The samples of every view in the wavefront's chunk of 8 bins from d0, the
+// sub-th of the slabs that lv holds.  False: no view may keep any.
+template <bool kRows>
+__device__ __forceinline__ bool fuse_chunk(FuseArgs a, const LiveViews &lv, uint32_t sub, int d0,
+                                           float px, float py, float (&S)[kFuseBins],
+                                           float (&Wo)[kFuseBins]) {
+  Chunk b;  // bins past D repeat the last one
+  const GG_CONSTANT float *bt = (const GG_CONSTANT float *)(const float *)(a->bins + d0);
+#pragma unroll
+  for (int v = 0; v < kFuseBins; ++v) {
+    b.z[v] = bt[2 * v];
+    b.tau[v] = bt[2 * v + 1];
+  }
+  uint64_t live = a->K ? 0x1111111111111111ull >> (64 - 4 * a->K) : 0ull, free = 0;
+  bool front = a->front != 0;
+  if (a->test) {
+    live = lv.of(lv.live, sub, a->K);
+    free = lv.of(lv.free, sub, a->K);
+    front = (lv.of(lv.behind, sub, a->K) & live) == 0;
+  }
+  const bool some = live != 0;
+#pragma nounroll
+  while (live) {
+    const int bit = __builtin_ctzll(live), k = __builtin_amdgcn_readfirstlane(bit >> 2);
+    live = uniform64(live & (live - 1));
+    if (!front)
+      fuse_any<kRows>(a, k, px, py, b, S, Wo);
+    else if ((free >> bit) & 1u)
+      fuse_front<kRows, true>(a, k, px, py, b, S, Wo);
+    else
+      fuse_front<kRows, false>(a, k, px, py, b, S, Wo);
+  }
+  return some;
+}
+
+// The place of a tile in the target.
+struct FuseTile {
+  uint32_t pix0, pix, last;  // first pixel, the lane's, the tile's last from the first
+  float px, py;              // the lane's pixel
+  TileRect rect;
+
+  __device__ __forceinline__ FuseTile(FuseArgs a, uint32_t tile) {
+    pix0 = tile * kFusePix;
+    pix = pix0 + (threadIdx.x & 63u);
+    last = min(kFusePix - 1u, a->npix - 1u - pix0);
+    const FastDiv wt = {a->wt_div.d, a->wt_div.m, a->wt_div.s};
+    const uint32_t y = fdiv(pix, wt), x = pix - y * wt.d;
+    px = (float)x + 0.5f;
+    py = (float)y + 0.5f;
+    // its part of one target row, or every column of the rows it runs over, taken at their middle
+    const uint32_t y0 = fdiv(pix0, wt), x0 = pix0 - y0 * wt.d, y1 = fdiv(pix0 + last, wt);
+    rect.x0 = (float)(y1 > y0 ? 0u : x0) + 0.5f;
+    rect.x1 = (float)(y1 > y0 ? wt.d - 1u : x0 + last) + 0.5f;
+    rect.y = 0.5f * (float)(y0 + y1) + 0.5f;
+    rect.ext = (float)(y1 - y0) * (0.5f * a->zfar);
+  }
+};
+
+// A tile in windows of a->span bins held in LDS, without a carry: where bins
+// do not make whole lines, so that a slab's stores would cut two lines of
+// every pixel.  Lines cut in time leave the caches half written, and such
+// stores bound the kernel.  Mostly one window holds all D bins: the tile's 64
+// runs are one contiguous piece of the volume, stored at the end.  With more
+// bins (a multiple of the wavefronts' per window) each pixel's run is stored
+// up to the last line that the window completes; its other bins, less than a
+// line, stay in LDS, a ring of span + 32 bins per pixel.
+template <int kForm>
+__device__ __forceinline__ void integrate_windows(FuseArgs a, uint32_t tile, float *smem) {
+  constexpr bool kRows = (kForm & kFormRows) != 0;
+  constexpr int kWide = (kForm & kFormVec) ? 4 : 1;
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  const int wave = (int)__builtin_amdgcn_readfirstlane(t >> 6), waves = (int)(blockDim.x >> 6);
+  const int D = a->D, step = waves * kFuseBins, span = a->span, ring = span < D ? span + 32 : D;
+  const uint32_t row = a->row;
+  float *vol[2] = {smem, smem + kFusePix * row};
+  unsigned long long *best = reinterpret_cast<unsigned long long *>(smem + 2 * kFusePix * row);
+  const FuseTile T(a, tile);
+  if (t < kFusePix) best[t] = ~0ull;
+  if (a->out_depth) __syncthreads();
+  LiveViews lv;
+  lv.shift = a->K > 1 ? 32u - (uint32_t)__builtin_clz((uint32_t)(a->K - 1)) : 0u;
+  lv.live = lv.free = lv.behind = 0;
+  int slab = 0, at0 = 0;  // at0: the place of bin w0 in the ring
+  for (int w0 = 0; w0 < D; w0 += span) {
+    const int w1 = min(w0 + span, D);
+    for (int d0 = w0 + wave * kFuseBins; d0 < w1; d0 += step, ++slab) {
+      a = reread(a);
+      float S[kFuseBins], Wo[kFuseBins];
+#pragma unroll
+      for (int v = 0; v < kFuseBins; ++v) S[v] = Wo[v] = 0.0f;
+      const uint32_t sub = (uint32_t)slab & (lv.slabs() - 1u);
+      if (a->test && sub == 0) find_live(a, T.rect, d0 / kFuseBins, waves, lv);
+      const bool some = fuse_chunk<kRows>(a, lv, sub, d0, T.px, T.py, S, Wo);
+      a = reread(a);
+      if (some) {
+#pragma unroll
+        for (int v = 0; v < kFuseBins; ++v) {
+          float mean = S[v] / Wo[v];
+          asm volatile("" : "+v"(mean));  // no branch around each division: they run abreast
+          S[v] = Wo[v] > 0.0f ? mean : 0.0f;
+        }
+      }
+      int at = at0 + (d0 - w0);  // (a chunk lies whole in the ring: both are multiples of 8)
+      if (at >= ring) at -= ring;
+      float *f = vol[0] + lane * row + at, *w = vol[1] + lane * row + at;
+      if constexpr (kWide == 4) {
+#pragma unroll
+        for (int q = 0; q < kFuseBins; q += 4)
+          if (d0 + q < w1) {
+            *(gg_v4f *)(f + q) = (gg_v4f){S[q], S[q + 1], S[q + 2], S[q + 3]};
+            *(gg_v4f *)(w + q) = (gg_v4f){Wo[q], Wo[q + 1], Wo[q + 2], Wo[q + 3]};
+          }
+      } else {
+#pragma unroll
+        for (int v = 0; v < kFuseBins; ++v)
+          if (d0 + v < w1) f[v] = S[v], w[v] = Wo[v];
+      }
+      if (a->out_depth && some) {
+        // the first crossing within the chunk
+        const GG_CONSTANT float *bt = (const GG_CONSTANT float *)(const float *)(a->bins + d0);
+        int d = -1;
+        float f0 = 1.0f, f1 = 0.0f, za = 0.0f, zb = 0.0f;
+#pragma unroll
+        for (int v = kFuseBins - 1; v >= 1; --v)
+          if (d0 + v < D && S[v - 1] > 0.0f && Wo[v] > 0.0f && S[v] <= 0.0f) {
+            d = d0 + v - 1;
+            f0 = S[v - 1];
+            f1 = S[v];
+            za = bt[2 * v - 2];
+            zb = bt[2 * v];
+          }
+        if (d >= 0) atomicMin(&best[lane], crossing_key(d, za, zb, f0, f1));
+      }
+    }
+    __syncthreads();  // the window is staged
+    float *out[2] = {a->F + (size_t)T.pix0 * (size_t)D, a->W + (size_t)T.pix0 * (size_t)D};
+    const uint32_t base[2] = {(uint32_t)((uintptr_t)out[0] >> 2), (uint32_t)((uintptr_t)out[1] >> 2)};
+    if (span >= D && row == (uint32_t)D && ((base[0] | base[1]) & 3u) == 0) {
+      // the tile's runs, as they lie in LDS
+      const uint32_t n = (T.last + 1u) * (uint32_t)D;
+      for (uint32_t e = 4u * t; e < n; e += 4u * blockDim.x) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (kWide == 4 || e + 4u <= n)
+            __builtin_nontemporal_store(*(const gg_v4f *)(vol[h] + e), (GG_GLOBAL gg_v4f *)(out[h] + e));
+          else
+            for (uint32_t i = e; i < n; ++i) gmem(out[h])[i] = vol[h][i];
+        }
+      }
+    } else {
+      // run by run, from a line's start (or the run's) to another's (or the run's end)
+      const int per = (span >= D ? D : span + 32) / kWide;  // accesses per run, at most
+      const int dp = (int)blockDim.x / per, dj = (int)blockDim.x - dp * per;
+      auto store_runs = [&](int h0, int h1) {
+        int p = (int)t / per, j = (int)t - p * per;
+        while (p <= (int)T.last) {
+          const uint32_t b = base[h0] + (uint32_t)(p * D);
+          const int lo = w0 > 0 ? w0 - (int)((b + (uint32_t)w0) & 31u) : 0;
+          const int hi = w1 < D ? w1 - (int)((b + (uint32_t)w1) & 31u) : D;
+          const int d = lo + j * kWide;
+          if (d < hi) {
+            int at = at0 + (d - w0);
+            if (at < 0) at += ring;
+            if (at >= ring) at -= ring;
+            for (int h = h0; h < h1; ++h) {
+              const float *from = vol[h] + (uint32_t)p * row + at;
+              GG_GLOBAL float *to = gmem(out[h]) + (p * D + d);
+              if constexpr (kWide == 4)
+                __builtin_nontemporal_store(*(const gg_v4f *)from, (GG_GLOBAL gg_v4f *)to);
+              else
+                __builtin_nontemporal_store(*from, to);
+            }
+          }
+          p += dp;
+          j += dj;
+          if (j >= per) {
+            j -= per;
+            ++p;
+          }
+        }
+      };
+      if (span >= D || ((base[0] ^ base[1]) & 31u) == 0) {  // F and W alike
+        store_runs(0, 2);
+      } else {
+        store_runs(0, 1);
+        store_runs(1, 2);
+      }
+    }
+    if (a->out_depth) {
+      // crossings between chunks (before the first bin of all there is none)
+      for (int d = w0 + wave * kFuseBins; d < w1; d += step) {
+        if (d == 0) continue;
+        int at = at0 + (d - w0);
+        if (at >= ring) at -= ring;
+        const float *f = vol[0] + lane * row, *w = vol[1] + lane * row;
+        const float f0 = f[at > 0 ? at - 1 : ring - 1], f1 = f[at];
+        if (f0 > 0.0f && w[at] > 0.0f && f1 <= 0.0f) {
+          const GG_CONSTANT float *bt = (const GG_CONSTANT float *)(const float *)(a->bins + d);
+          atomicMin(&best[lane], crossing_key(d - 1, bt[-2], bt[0], f0, f1));
+        }
+      }
+    }
+    if (w1 < D) __syncthreads();  // the window has been read
+    at0 += span;
+    if (at0 >= ring) at0 -= ring;
+  }
+  if (a->out_depth) {
+    __syncthreads();
+    if (t < kFusePix && T.pix < a->npix) {
+      const unsigned long long key = best[t];
+      gmem(a->out_depth)[T.pix] = key == ~0ull ? 0.0f : __uint_as_float((uint32_t)key);
+      gmem(a->out_bin)[T.pix] = key == ~0ull ? -1 : (int32_t)(key >> 32);
+    }
+  }
+}
+
 // Tile `tile` (kFusePix pixels) of one target, in the form of integrate_form.
 template <int kForm>
 __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float *smem) {
+  if constexpr ((kForm & kFormWindows) != 0) return integrate_windows<kForm>(a, tile, smem);
   constexpr bool kCarry = (kForm & kFormCarry) != 0, kRows = (kForm & kFormRows) != 0;
   constexpr bool kLines = (kForm & kFormLines) != 0, kVec = (kForm & kFormVec) != 0;
   constexpr bool kDirect = kCarry && kLines;
@@ -521,26 +790,14 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
   const int wave = (int)__builtin_amdgcn_readfirstlane(t >> 6), waves = (int)(blockDim.x >> 6);
   const FuseLds L(smem, waves);
   const int D = a->D;
-  const uint32_t pix0 = tile * kFusePix, pix = pix0 + lane;
-  const uint32_t last = min(kFusePix - 1u, a->npix - 1u - pix0);  // the tile's last pixel
-  const FastDiv wt = {a->wt_div.d, a->wt_div.m, a->wt_div.s};
-  const uint32_t y = fdiv(pix, wt), x = pix - y * wt.d;
-  const float px = (float)x + 0.5f, py = (float)y + 0.5f;
-  // the tile's rectangle: its part of one target row, or every column of the
-  // rows it runs over, taken at their middle
-  const uint32_t y0 = fdiv(pix0, wt), x0 = pix0 - y0 * wt.d, y1 = fdiv(pix0 + last, wt);
-  TileRect rect;
-  rect.x0 = (float)(y1 > y0 ? 0u : x0) + 0.5f;
-  rect.x1 = (float)(y1 > y0 ? wt.d - 1u : x0 + last) + 0.5f;
-  rect.y = 0.5f * (float)(y0 + y1) + 0.5f;
-  rect.ext = (float)(y1 - y0) * (0.5f * a->zfar);
+  const FuseTile T(a, tile);
   if (t < kFusePix) L.best[t] = ~0ull;  // the first slab's barriers precede its use
   float m = 1.0f;
-  if (kCarry && a->mask) m = fmaxf(1.0f - gmem(a->mask)[min(pix, a->npix - 1u)], 0.0f);
+  if (kCarry && a->mask) m = fmaxf(1.0f - gmem(a->mask)[min(T.pix, a->npix - 1u)], 0.0f);
 
   typedef std::conditional_t<kDirect, SlabDirect, SlabRows<kVec, kLines>> Slab;
-  const Slab slabs((uint32_t)waves, last, D);
-  const size_t base = (size_t)pix0 * (size_t)D;
+  const Slab slabs((uint32_t)waves, T.last, D);
+  const size_t base = (size_t)T.pix0 * (size_t)D;
   typename Slab::Held rF, rW;
   // the previous volume's slab from s0
   auto load_volume = [&](int s0) {
@@ -561,37 +818,10 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
 #pragma unroll
     for (int v = 0; v < kFuseBins; ++v) S[v] = Wo[v] = 0.0f;
     const uint32_t sub = (uint32_t)slab & (lv.slabs() - 1u);
-    if (a->test && sub == 0) find_live(a, rect, slab * waves + wave, waves, lv);
+    if (a->test && sub == 0) find_live(a, T.rect, slab * waves + wave, waves, lv);
     // without a view and a volume to carry, the chunk is zero and has no crossing
     bool some = kCarry;
-    if (d0 < D) {
-      Chunk b;  // bins past D repeat the last one
-      const GG_CONSTANT float *bt = (const GG_CONSTANT float *)(const float *)(a->bins + d0);
-#pragma unroll
-      for (int v = 0; v < kFuseBins; ++v) {
-        b.z[v] = bt[2 * v];
-        b.tau[v] = bt[2 * v + 1];
-      }
-      uint64_t live = a->K ? 0x1111111111111111ull >> (64 - 4 * a->K) : 0ull, free = 0;
-      bool front = a->front != 0;
-      if (a->test) {
-        live = lv.of(lv.live, sub, a->K);
-        free = lv.of(lv.free, sub, a->K);
-        front = (lv.of(lv.behind, sub, a->K) & live) == 0;
-      }
-      some = some || live != 0;
-#pragma nounroll
-      while (live) {
-        const int bit = __builtin_ctzll(live), k = __builtin_amdgcn_readfirstlane(bit >> 2);
-        live = uniform64(live & (live - 1));
-        if (!front)
-          fuse_any<kRows>(a, k, px, py, b, S, Wo);
-        else if ((free >> bit) & 1u)
-          fuse_front<kRows, true>(a, k, px, py, b, S, Wo);
-        else
-          fuse_front<kRows, false>(a, k, px, py, b, S, Wo);
-      }
-    }
+    if (d0 < D) some |= fuse_chunk<kRows>(a, lv, sub, d0, T.px, T.py, S, Wo);
     a = reread(a);
     if constexpr (kCarry) {
       slabs.arrive(L.vol[0], rF);
@@ -687,10 +917,10 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
   }
   if (a->out_depth) {
     __syncthreads();
-    if (t < kFusePix && pix < a->npix) {
+    if (t < kFusePix && T.pix < a->npix) {
       const unsigned long long key = L.best[t];
-      gmem(a->out_depth)[pix] = key == ~0ull ? 0.0f : __uint_as_float((uint32_t)key);
-      gmem(a->out_bin)[pix] = key == ~0ull ? -1 : (int32_t)(key >> 32);
+      gmem(a->out_depth)[T.pix] = key == ~0ull ? 0.0f : __uint_as_float((uint32_t)key);
+      gmem(a->out_bin)[T.pix] = key == ~0ull ? -1 : (int32_t)(key >> 32);
     }
   }
 }

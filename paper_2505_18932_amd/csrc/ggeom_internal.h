@@ -241,6 +241,8 @@ struct IntegrateArgs {
   int32_t test;        // 1: find_live applies
   int32_t front;       // 1: every sample of every view is in front of its camera
   float zfar;          // above every bin depth
+  uint32_t row;        // forms with windows (integrate_windows): floats per pixel of F or W in LDS
+  int32_t span;        // and bins per window
 };
 
 struct ExtractArgs {
@@ -323,7 +325,7 @@ int launch_blend(const BlendArgs &a, hipStream_t s);
 int launch_bins(const gg_tsdf_params &p, float2 *bins, uint32_t *cells, uint32_t ncells,
                 hipStream_t s);
 int launch_conf(const ConfArgs &a, hipStream_t s);
-int launch_integrate(const IntegrateArgs &a, hipStream_t s);
+int launch_integrate(IntegrateArgs &a, hipStream_t s);
 // Which form of the fusion kernel a launch takes (bits of its template arguments).
 int integrate_form(const IntegrateArgs &a);
 int launch_extract(const ExtractArgs &a, hipStream_t s);

@@ -74,7 +74,7 @@ int launch_conf(const ConfArgs &a, hipStream_t s) {
 }
 
 template <int kForm>
-__global__ __launch_bounds__(64 * kFuseMaxWaves) void integrate_kernel(IntegrateArgs args) {
+__global__ __launch_bounds__(64 * kFuseMaxWaves, form_waves(kForm)) void integrate_kernel(IntegrateArgs args) {
   extern __shared__ __align__(16) float smem[];
   // the record is read in the argument segment (offset 0: the only argument)
   const FuseArgs a = (FuseArgs)__builtin_amdgcn_kernarg_segment_ptr();
@@ -87,23 +87,27 @@ __global__ __launch_bounds__(64 * kFuseMaxWaves) void integrate_kernel(Integrate
 int integrate_form(const IntegrateArgs &a) {
   auto al = [](const void *p) { return ((uintptr_t)p & 15u) == 0; };
   const bool vec = a.D % 4 == 0 && al(a.F) && al(a.W) && al(a.F_prev) && al(a.W_prev);
-  return (vec ? kFormVec : 0) | (vec && a.D % 32 == 0 ? kFormLines : 0) |
-         (table_rows_ok(a.Ws) ? kFormRows : 0) | (a.F_prev ? kFormCarry : 0);
+  const bool lines = vec && a.D % 32 == 0, carry = a.F_prev != nullptr;
+  return (vec ? kFormVec : 0) | (lines ? kFormLines : 0) | (table_rows_ok(a.Ws) ? kFormRows : 0) |
+         (carry ? kFormCarry : 0) |
+         (!lines && !carry && fuse_windows(a.K, a.D, vec, a.npix) ? kFormWindows : 0);
 }
 
 template <int kForm>
-static void launch_form(const IntegrateArgs &a, int form, hipStream_t s) {
+static void launch_form(IntegrateArgs &a, int form, hipStream_t s) {
   if constexpr (kForm < kFuseForms) {
     if (form != kForm) return launch_form<kForm + 1>(a, form, s);
     if constexpr (form_exists(kForm)) {
-      const int waves = fuse_waves(a.D, a.nblocks, form_direct(kForm));
-      hipLaunchKernelGGL(integrate_kernel<kForm>, dim3(a.nblocks), dim3(64 * waves),
-                         FuseLds::bytes(waves), s, a);
+      const FuseShape shape = fuse_shape(kForm, a.K, a.D, a.nblocks);
+      a.row = shape.row;
+      a.span = shape.span;
+      hipLaunchKernelGGL(integrate_kernel<kForm>, dim3(a.nblocks), dim3(64 * shape.waves),
+                         shape.lds, s, a);
     }
   }
 }
 
-int launch_integrate(const IntegrateArgs &a, hipStream_t s) {
+int launch_integrate(IntegrateArgs &a, hipStream_t s) {
   KernelTimer t("integrate", s);
   launch_form<0>(a, integrate_form(a), s);
   return check_hip(hipGetLastError(), "integrate_kernel");
