@@ -240,7 +240,8 @@ __device__ __forceinline__ void accumulate(float Z, float2 e, float tau, float &
   Wo = Wo + w;
 }
 
-// One view in front of every lane: the eight gathers are issued as their
+// One view in front of every lane (each view by itself: one that reaches behind
+// its camera leaves the others this form): the eight gathers are issued as their
 // addresses are formed (two at a time: few registers, and the other
 // wavefronts fill the latencies), then accumulated.  kFree: every usable
 // sample lies at least tau in front of its surface, so the clamp gives tau
@@ -577,18 +578,18 @@ __device__ __forceinline__ bool fuse_chunk(FuseArgs a, const LiveViews &lv, uint
     b.tau[v] = bt[2 * v + 1];
   }
   uint64_t live = a->K ? 0x1111111111111111ull >> (64 - 4 * a->K) : 0ull, free = 0;
-  bool front = a->front != 0;
+  uint64_t behind = a->front ? 0ull : live;
   if (a->test) {
     live = lv.of(lv.live, sub, a->K);
     free = lv.of(lv.free, sub, a->K);
-    front = (lv.of(lv.behind, sub, a->K) & live) == 0;
+    behind = lv.of(lv.behind, sub, a->K);
   }
   const bool some = live != 0;
 #pragma nounroll
   while (live) {
     const int bit = __builtin_ctzll(live), k = __builtin_amdgcn_readfirstlane(bit >> 2);
     live = uniform64(live & (live - 1));
-    if (!front)
+    if ((behind >> bit) & 1u)
       fuse_any<kRows>(a, k, px, py, b, S, Wo);
     else if ((free >> bit) & 1u)
       fuse_front<kRows, true>(a, k, px, py, b, S, Wo);
