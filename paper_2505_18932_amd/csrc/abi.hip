@@ -828,6 +828,13 @@ static void make_integrate_args(IntegrateArgs &a, const gg_camera *src, int32_t 
   a.front = a.test && front;
 }
 
+// Whether the launch reads the cells' ranges; without them it looks for views to drop only where a
+// sample may lie behind its camera, which the test must find.
+static void use_ranges(IntegrateArgs &a, bool ranges) {
+  a.test = a.test && (ranges || !a.front);
+  if (!a.test || !ranges) a.cells = nullptr;
+}
+
 // The cells' place in a workspace of ws_bytes (null if it ends before them).  Whether they hold
 // the table's ranges is for the table to say (closing_record): it may come from another call.
 static uint32_t *cells_of(const TsdfLayout &L, char *w, size_t ws_bytes) {
@@ -893,9 +900,9 @@ static int integrate_impl(const char *N, bool tabled, const gg_camera *src, int3
   IntegrateArgs a{};
   make_integrate_args(a, src, K, *tgt, *prm, band_pixels(tuning), table, bins, (const float *)cells,
                       temporal_mask, F_prev, W_prev, F, W, out_depth, out_bin);
-  a.test = a.test && fuse_tests(K, a.nblocks, a.front != 0);
+  use_ranges(a, fuse_ranges(K, a.nblocks, D));
   if (!tabled)
-    if (int rc = build_view_table(src, K, depth, prm, L, w, a.test ? cells : nullptr, s)) return rc;
+    if (int rc = build_view_table(src, K, depth, prm, L, w, a.cells ? cells : nullptr, s)) return rc;
   return launch_integrate(a, s);
 }
 
@@ -1441,7 +1448,7 @@ extern "C" int gg_batch_plan(const gg_batch_item *items, int32_t n, const gg_bat
     const FuseShape shape = fuse_shape(integrate_form(d.integ), it.K, d.integ.D, UINT32_MAX);
     d.integ.row = shape.row;
     d.integ.span = shape.span;
-    d.integ.test = d.integ.test && fuse_tests(it.K, UINT32_MAX, d.integ.front != 0);
+    use_ranges(d.integ, fuse_ranges(it.K, UINT32_MAX, d.integ.D));
     if (it.rgb) {
       make_splat_args(d.splat, it.src, it.K, it.depth, it.rgb, it.tgt, it.splat, sl[i],
                       dv + o_splat[i]);

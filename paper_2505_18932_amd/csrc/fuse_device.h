@@ -40,14 +40,16 @@ __host__ __device__ inline int fuse_waves(int D, uint32_t nblocks, bool direct) 
   return w;
 }
 
-// Whether a launch looks for views to drop (find_live) where it may: with one
-// or two views there is too little to drop, and in small launches, a round or
-// so of workgroups, the test's chain of loads is not hidden (measured, with
-// and without: 1280 x 720 K=1 D=128 207 and 185 us, 640 x 400 K=2 D=64 43 and
-// 40, 420 x 260 K=3 D=48 26.9 and 25.1; 512 x 288 K=4 D=96 50 and 53).  It may
-// not be left out where a sample can be behind its camera.
-__host__ __device__ inline bool fuse_tests(int K, uint32_t nblocks, bool front) {
-  return !front || (K > 2 && nblocks > 1536);
+// Whether a launch reads the cells' depth ranges (find_live).  The more views
+// and the more chunks of 64 pixels x 8 bins there are, the more it drops and
+// the better the test's chain of loads is hidden.  Measured, with and without:
+// 1280 x 720 K=1 D=128 207 and 185 us, 640 x 400 K=2 D=64 43 and 40; 420 x 260
+// K=3 D=48 (10 242 chunks) 35.5 and 30.9, 640 x 360 K=4 D=64 (28 800) 72.1 and
+// 69.5, K=6 D=48 (21 600) 88.4 and 85.0, but K=4 D=100 (46 800) 95.3 and 96.3,
+// 800 x 450 K=3 D=128 (90 000) 124.8 and 131.4.
+__host__ __device__ inline bool fuse_ranges(int K, uint32_t nblocks, int D) {
+  const uint64_t chunks = (uint64_t)nblocks * (uint32_t)((D + kFuseBins - 1) / kFuseBins);
+  return K > 2 && chunks * (uint32_t)(K - 2) > 80000;
 }
 
 // LDS of a workgroup, in floats: F and W of the slab, F of each chunk's last
