@@ -31,11 +31,14 @@ constexpr int kFuseMaxWaves = 16;   // of a workgroup (LDS of slabs: 79 KB)
 // with four; 640 x 400 K=4 D=100: 139 us with thirteen and a single slab, 95
 // with four).  Launches of no more workgroups than run at once take eight or
 // sixteen: their slabs would run one after the other beside idle wavefronts
-// (measured, 160 x 100 K=4 D=256: 54 us with four, 27 with sixteen).
-__host__ __device__ inline int fuse_waves(int D, uint32_t nblocks, bool direct) {
+// (measured, 160 x 100 K=4 D=256: 54 us with four, 27 with sixteen).  Without a
+// carry, whose registers leave room for six wavefronts per SIMD, eight run at
+// once in up to 768 (240 x 150 K=4 D=128 32.2 us with four, 29.8 with eight;
+// carried, 2% slower over D = 16 to 192).
+__host__ __device__ inline int fuse_waves(int D, uint32_t nblocks, bool direct, bool carry) {
   const int chunks = (D + kFuseBins - 1) / kFuseBins;
-  // 256 compute units of 20 wavefronts (24 in some forms): one workgroup of 16 or two of 8 each
-  int w = nblocks <= 256 ? (direct ? 8 : 16) : (nblocks <= 512 ? 8 : 4);
+  // 256 compute units of 16 to 24 wavefronts: one workgroup of 16, or two or three of 8
+  int w = nblocks <= 256 ? (direct ? 8 : 16) : (nblocks <= (carry ? 512 : 768) ? 8 : 4);
   while (w > 1 && w / 2 >= chunks) w /= 2;
   return w;
 }
@@ -117,9 +120,11 @@ struct FuseShape {
 // 117 us; D=100 with 7, 8, 12 and 13 180, 169, 187 and 266; D=125 with 8, 12 and 16 239, 225 and
 // 320).  More than 156 bins leave one workgroup per compute unit: vector accesses of two or more
 // views then take windows of 64 bins, three workgroups (1280 x 720 D=200 K=4 734 and 566, K=2 580
-// and 461; K=1 446 and 452; single floats of D=233 K=4 821 and 1065: one window).
+// and 461; K=1 446 and 452; single floats of D=233 K=4 821 and 1065: one window).  Small launches
+// take as many wavefronts as run at once, few bins a wavefront per chunk (240 x 150 K=4 D=16 with
+// one 18.4 us, with two 14.9).
 __host__ inline FuseShape fuse_shape(int form, int K, int D, uint32_t nblocks) {
-  FuseShape s{fuse_waves(D, nblocks, form_direct(form)), 0, 0u, 0};
+  FuseShape s{fuse_waves(D, nblocks, form_direct(form), (form & kFormCarry) != 0), 0, 0u, 0};
   s.lds = FuseLds::bytes(s.waves);
   if (form & kFormWindows) {
     const int chunks = (D + kFuseBins - 1) / kFuseBins;
@@ -127,11 +132,14 @@ __host__ inline FuseShape fuse_shape(int form, int K, int D, uint32_t nblocks) {
     if (nblocks > 512) {
       const int rounds = (chunks + kFuseMaxWaves - 1) / kFuseMaxWaves;
       s.waves = D > 64 && D <= 108 ? 8 : D > 64 && !more ? 12 : (chunks - 1) / (rounds > 2 ? rounds : 2) + 1;
+      // all that run at once, and a chunk each where there are few
+      const int room = (int)(256u * 24u / nblocks), least = D <= 24 ? chunks : (room < chunks ? room : chunks);
+      if (s.waves < least) s.waves = least;
     }
     s.span = kFuseBins * chunks;
     if (D > kFuseWhole || (more && K > 1 && nblocks > 512 && (form & kFormVec))) {
-      s.waves = 8;
-      s.span = 64;
+      s.waves = nblocks <= 256 ? 16 : 8;
+      s.span = kFuseBins * s.waves;
     }
     s.row = (uint32_t)(s.span < D ? s.span + 36 : D);  // a ring's padded against bank conflicts
     s.lds = sizeof(float) * (2 * kFusePix * s.row + 2 * kFusePix);
