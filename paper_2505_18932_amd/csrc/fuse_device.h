@@ -258,19 +258,20 @@ __device__ __forceinline__ void accumulate(float Z, float2 e, float tau, float &
 // whatever the depth and only the weights count (no pixel or a hole: 0).
 // Whole records all the same: 4-byte gathers at this stride hold the texture
 // address unit longer than 8-byte ones (measured: 76 to 97 us at 640 x 360 K=4 D=96).
-template <bool kRows, bool kFree>
+// kN: the chunk's bins, the last chunk's four where it has no more.
+template <bool kRows, bool kFree, int kN>
 __device__ __forceinline__ void fuse_front(FuseArgs a, int k, float px, float py, const Chunk &b,
                                            float (&S)[kFuseBins], float (&Wo)[kFuseBins]) {
   const FuseView view = fuse_view<kRows>(a, k, px, py);
-  float Z[kFuseBins];
-  float2 e[kFuseBins];
+  float Z[kN];
+  float2 e[kN];
 #pragma unroll
-  for (int v = 0; v < kFuseBins; ++v) {
+  for (int v = 0; v < kN; ++v) {
     e[v] = front_sample<kRows>(view, b.z[v], Z[v]);
     if (v & 1) schedule_fence();
   }
 #pragma unroll
-  for (int v = 0; v < kFuseBins; ++v) {
+  for (int v = 0; v < kN; ++v) {
     if constexpr (kFree) {
       asm volatile("" ::"v"(e[v].x));  // keeps the whole record's load
       S[v] = fmaf(e[v].y, b.tau[v], S[v]);
@@ -575,8 +576,10 @@ __device__ __forceinline__ unsigned long long crossing_key(int d, float za, floa
 }
 
 // The samples of every view in the wavefront's chunk of 8 bins from d0, the
-// sub-th of the slabs that lv holds.  False: no view may keep any.
-template <bool kRows>
+// sub-th of the slabs that lv holds.  False: no view may keep any.  kWhole: D
+// is a multiple of 8.  Else a last chunk of at most four bins samples only four
+// (measured, all eight and four: 1280 x 720 K=4 D=2 64 and 52 us).
+template <bool kRows, bool kWhole>
 __device__ __forceinline__ bool fuse_chunk(FuseArgs a, const LiveViews &lv, uint32_t sub, int d0,
                                            float px, float py, float (&S)[kFuseBins],
                                            float (&Wo)[kFuseBins]) {
@@ -594,17 +597,19 @@ __device__ __forceinline__ bool fuse_chunk(FuseArgs a, const LiveViews &lv, uint
     free = lv.of(lv.free, sub, a->K);
     behind = lv.of(lv.behind, sub, a->K);
   }
-  const bool some = live != 0;
+  const bool some = live != 0, half = !kWhole && a->D - d0 <= 4;
 #pragma nounroll
   while (live) {
     const int bit = __builtin_ctzll(live), k = __builtin_amdgcn_readfirstlane(bit >> 2);
     live = uniform64(live & (live - 1));
     if ((behind >> bit) & 1u)
       fuse_any<kRows>(a, k, px, py, b, S, Wo);
+    else if (half)
+      fuse_front<kRows, false, 4>(a, k, px, py, b, S, Wo);
     else if ((free >> bit) & 1u)
-      fuse_front<kRows, true>(a, k, px, py, b, S, Wo);
+      fuse_front<kRows, true, kFuseBins>(a, k, px, py, b, S, Wo);
     else
-      fuse_front<kRows, false>(a, k, px, py, b, S, Wo);
+      fuse_front<kRows, false, kFuseBins>(a, k, px, py, b, S, Wo);
   }
   return some;
 }
@@ -666,7 +671,7 @@ __device__ __forceinline__ void integrate_windows(FuseArgs a, uint32_t tile, flo
       for (int v = 0; v < kFuseBins; ++v) S[v] = Wo[v] = 0.0f;
       const uint32_t sub = (uint32_t)slab & (lv.slabs() - 1u);
       if (a->test && sub == 0) find_live(a, T.rect, d0 / kFuseBins, waves, lv);
-      const bool some = fuse_chunk<kRows>(a, lv, sub, d0, T.px, T.py, S, Wo);
+      const bool some = fuse_chunk<kRows, false>(a, lv, sub, d0, T.px, T.py, S, Wo);
       a = reread(a);
       if (some) {
 #pragma unroll
@@ -832,7 +837,7 @@ __device__ __forceinline__ void integrate_tile(FuseArgs a, uint32_t tile, float 
     if (a->test && sub == 0) find_live(a, T.rect, slab * waves + wave, waves, lv);
     // without a view and a volume to carry, the chunk is zero and has no crossing
     bool some = kCarry;
-    if (d0 < D) some |= fuse_chunk<kRows>(a, lv, sub, d0, T.px, T.py, S, Wo);
+    if (d0 < D) some |= fuse_chunk<kRows, kLines>(a, lv, sub, d0, T.px, T.py, S, Wo);
     a = reread(a);
     if constexpr (kCarry) {
       slabs.arrive(L.vol[0], rF);
