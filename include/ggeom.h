@@ -111,9 +111,9 @@ typedef struct gg_mask_params {
  *                     across, each walked row by row from the top, so that
  *                     the view-table lines which neighbouring target rows
  *                     share are still cached when the next row needs them;
- *                     0..65536 (0: 256); a band as wide as the target is
- *                     plain row-major order, which is also taken where the
- *                     target width is not a multiple of 64.
+ *                     0..65536 (0: 256, or row-major where that suits the
+ *                     sizes better); a band as wide as the target is plain
+ *                     row-major order.
  * Invalid values: GG_ERR_INVALID. */
 typedef struct gg_volume_tuning {
   int32_t pixels_per_block;
@@ -482,9 +482,8 @@ typedef struct gg_batch_item {
   float *sp_depth, *sp_rgb, *sp_alpha;
   float *sp_tape;               /* or NULL                                           */
   gg_volume_tuning volume;      /* this item's fusion launch shape, as tsdf_integrate
-                                   takes it (all 0: the plan's bins_per_thread, bands
-                                   of 256 pixels); invalid values fail the plan with
-                                   GG_ERR_INVALID                                   */
+                                   takes it (all 0: the plan's bins_per_thread);
+                                   invalid values fail the plan with GG_ERR_INVALID */
 } gg_batch_item;
 
 /* Launch shape chosen by the autotuner (0 = default). */

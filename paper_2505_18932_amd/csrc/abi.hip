@@ -357,22 +357,22 @@ static int check_tuning(const gg_volume_tuning *t, const char *what) {
   return GG_OK;
 }
 
-constexpr uint32_t kDefaultBandPixels = 256;
-static uint32_t band_pixels(const gg_volume_tuning *t) {
-  return t && t->band_width > 0 ? (uint32_t)t->band_width : kDefaultBandPixels;
-}
+static uint32_t band_pixels(const gg_volume_tuning *t) { return t ? (uint32_t)t->band_width : 0u; }
 
 // The fusion's tile order (IntegrateArgs::band_*) for a target of width x
-// height pixels: bands of band_px pixels across where whole tiles make up
-// each row, else row-major.
+// height pixels: bands of band_px pixels across, row-major where one band is
+// as wide as the target.  0: bands of 256, but row-major where the width is no
+// multiple of 64 (the last band is narrow, and its tiles straddle two rows)
+// and the view tables fit the L2 caches, 32 MB together, or are of one or two
+// views (row-major order and bands: 420 x 260 K=3 (3 MB) D=64 31.4 and 32.4 us, 637 x 359 K=8 (15 MB)
+// D=128 147.5 and 148.5, 1529 x 1031 K=2 (25 MB) D=100 322 and 335; but 900 x
+// 500 K=8 (29 MB) D=128 300 and 256, 1529 x 1031 K=8 D=36 722 and 375).
 static void set_band_order(IntegrateArgs &a, int width, int height, uint32_t band_px) {
-  a.band_T = a.band_B = a.band_H = 0;
-  if ((uint32_t)width % kFusePix != 0) return;
-  const uint32_t T = (uint32_t)width / kFusePix;
-  const uint32_t B = std::max(1u, band_px / kFusePix);
-  if (B >= T) return;
-  a.band_T = T;
-  a.band_B = B;
+  const size_t table = sizeof(float2) * table_view_records(a.Ws, a.Hs) * (size_t)a.K;
+  const bool rows = band_px == 0 && (uint32_t)width % kFusePix != 0 && (a.K <= 2 || table < (size_t)24 << 20);
+  const uint32_t B = rows ? (uint32_t)width : std::max(1u, (band_px ? band_px : 256u) / kFusePix);
+  a.band_N = (uint32_t)width / (B * kFusePix);
+  a.band_B = B * kFusePix < (uint32_t)width ? B : 0;
   a.band_H = (uint32_t)height;
 }
 

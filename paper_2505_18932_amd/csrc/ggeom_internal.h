@@ -233,9 +233,9 @@ struct IntegrateArgs {
   uint32_t npix;     // Ht * Wt
   FastDiv wt_div;    // by Wt
   uint32_t nblocks;
-  // tile order: band_T tiles per target row, visited in vertical bands of
-  // band_B tiles across and band_H rows (band_T = 0: row-major)
-  uint32_t band_T, band_B, band_H;
+  // tile order: vertical bands of band_B tiles across and band_H rows, band_N
+  // full ones and the rest of the width (band_B = 0: row-major)
+  uint32_t band_N, band_B, band_H;
   float decay, cap;
   int32_t exact_only;  // 1: every sample takes IEEE division (extreme depths)
   int32_t test;        // 1: find_live applies

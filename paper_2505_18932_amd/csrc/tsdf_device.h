@@ -262,17 +262,19 @@ __device__ __forceinline__ void conf_tile(const ConfArgs &a, int k, int bx, int 
 // bands of band_B tiles across, each row by row from the top, keeps the
 // lines that the tiles in flight share within cache, where row-major order
 // would have walked the whole target width before returning to them.
-// Every full band comes before the narrower last one (band_T = 0:
-// row-major order).
+// band_N full bands come before the narrower last one (band_B = 0: row-major
+// order).  A row's tiles of a band are those that start in it: of a full band
+// always band_B, of the last, wl columns wide, ceil(r wl / 64) in the rows
+// before row r, whether or not whole tiles make up a row (1529 x 1031 K=8 D=36
+// carried: row-major 912 us, in bands 690).
 __host__ __device__ __forceinline__ uint32_t band_tile(const IntegrateArgs &a, uint32_t s) {
-  if (a.band_T == 0) return s;
-  const uint32_t span = a.band_B * a.band_H;  // tiles of a full band
-  const uint32_t b = s / span;
-  const uint32_t b0 = b * a.band_B;
-  const uint32_t w = a.band_T - b0 < a.band_B ? a.band_T - b0 : a.band_B;
-  const uint32_t rem = s - b * span;
-  const uint32_t r = rem / w;
-  return r * a.band_T + b0 + (rem - r * w);
+  if (a.band_B == 0) return s;
+  const uint32_t w = a.wt_div.d, across = a.band_B * kFusePix, span = a.band_B * a.band_H;
+  uint32_t b = s / span;
+  if (b > a.band_N) b = a.band_N;
+  const uint32_t m = s - b * span, wl = b < a.band_N ? across : w - a.band_N * across;
+  const uint32_t r = kFusePix * m / wl;
+  return (r * w + b * across + kFusePix - 1) / kFusePix + m - (r * wl + kFusePix - 1) / kFusePix;
 }
 
 // ---------------------------------------------------------------------------
