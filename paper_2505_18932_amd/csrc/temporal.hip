@@ -4,9 +4,9 @@
 //      both frames (exact integers), the channel mean of |I - I'| and the
 //      clamped mask;
 //   2. one thread per low-resolution pixel: the 3 x 3 maximum;
-//   3. one thread per four full-resolution pixels: bilinear upsampling, and the
-//      depth filter fused in (one read of D and of the previous filtered
-//      depth, one write of each output).
+//   3. one thread per four full-resolution pixels (one where four are not
+//      aligned): bilinear upsampling, and the depth filter fused in (one read
+//      of D and of the previous filtered depth, one write of each output).
 // The low-resolution planes (1/16 of a frame) stay in L2 between passes.
 // Bound by latency and instructions, not bytes (4 x 1280 x 720, factor 4: 42 us
 // with a pixel per thread, 64-bit index divisions and byte loads, 25 with four
@@ -86,23 +86,24 @@ __global__ __launch_bounds__(256) void mask_pool_kernel(MaskArgs a) {
   gmem(a.pool)[((size_t)k * a.Hq + b) * a.Wq + aa] = m;
 }
 
-// Four pixels of a row per thread.  kWide: a factor of at least 4, so that
-// the four pixels' low-resolution columns are three neighbours, loaded once;
-// kVec: 16-byte accesses (the width a multiple of 4, the planes aligned).
+// kPer pixels of a row per thread: four by 16-byte accesses (the width a
+// multiple of 4, the planes aligned), else one, so that a wavefront's single
+// floats are neighbours (measured, 4 x 1283 x 721 factor 4: 36 us with four
+// single floats per thread, 30 with one).  kWide: of four pixels at a factor
+// of at least 4 the low-resolution columns are three neighbours, loaded once.
 // (i + 0.5) / factor is the product with 1 / factor, exact, for a power of two.
-template <bool kWide, bool kVec>
+template <bool kWide, int kPer>
 __global__ __launch_bounds__(256) void mask_up_kernel(MaskArgs a) {
-  const int i0 = 4 * (int)(blockIdx.x * kMaskX + (threadIdx.x & 63u));
+  const int i0 = kPer * (int)(blockIdx.x * kMaskX + (threadIdx.x & 63u));
   const int j = (int)(blockIdx.y * kMaskY + (threadIdx.x >> 6)), k = (int)blockIdx.z;
   if (i0 >= a.W || j >= a.H) return;
   const float fac = (float)a.factor, xmax = (float)(a.Wq - 1), ymax = (float)(a.Hq - 1);
   const bool pow2 = (a.factor & (a.factor - 1)) == 0;
   const float inv = 1.0f / fac;
   const size_t o = ((size_t)k * a.H + j) * a.W + i0;
-  const int n = min(4, a.W - i0);
-  float D[4] = {}, pv[4] = {};
+  float D[kPer] = {}, pv[kPer] = {};
   if (a.depth) {
-    if constexpr (kVec) {
+    if constexpr (kPer == 4) {
       const gg_v4f d = *(const GG_GLOBAL gg_v4f *)(a.depth + o);
       D[0] = d.x; D[1] = d.y; D[2] = d.z; D[3] = d.w;
       if (a.prev) {
@@ -110,12 +111,8 @@ __global__ __launch_bounds__(256) void mask_up_kernel(MaskArgs a) {
         pv[0] = p.x; pv[1] = p.y; pv[2] = p.z; pv[3] = p.w;
       }
     } else {
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (v < n) {
-          D[v] = gmem(a.depth)[o + v];
-          if (a.prev) pv[v] = gmem(a.prev)[o + v];
-        }
+      D[0] = gmem(a.depth)[o];
+      if (a.prev) pv[0] = gmem(a.prev)[o];
     }
   }
   auto low = [&](int i, float most) {  // the low-resolution coordinate
@@ -137,9 +134,9 @@ __global__ __launch_bounds__(256) void mask_up_kernel(MaskArgs a) {
       u[c] = p1[min(first + c, a.Wq - 1)];
     }
   }
-  float M[4], out[4];
+  float M[kPer], out[kPer];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
+  for (int v = 0; v < kPer; ++v) {
     const float x = low(i0 + v, xmax);
     const int x0 = (int)floorf(x), x1 = min(x0 + 1, a.Wq - 1);
     const float fx = x - (float)x0;
@@ -153,16 +150,12 @@ __global__ __launch_bounds__(256) void mask_up_kernel(MaskArgs a) {
     if (depth_ok(D[v]))
       out[v] = (pv[v] > 0.0f && pv[v] < INFINITY) ? fmaf(M[v], D[v], (1.0f - M[v]) * pv[v]) : D[v];
   }
-  if constexpr (kVec) {
+  if constexpr (kPer == 4) {
     *(GG_GLOBAL gg_v4f *)(a.mask + o) = (gg_v4f){M[0], M[1], M[2], M[3]};
     if (a.depth) *(GG_GLOBAL gg_v4f *)(a.filtered + o) = (gg_v4f){out[0], out[1], out[2], out[3]};
   } else {
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (v < n) {
-        gmem(a.mask)[o + v] = M[v];
-        if (a.depth) gmem(a.filtered)[o + v] = out[v];
-      }
+    gmem(a.mask)[o] = M[0];
+    if (a.depth) gmem(a.filtered)[o] = out[0];
   }
 }
 
@@ -171,7 +164,7 @@ int launch_difference_masks(const MaskArgs &a, hipStream_t s) {
   const auto grid = [&](int w, int h) {
     return dim3((w + kMaskX - 1) / kMaskX, (h + kMaskY - 1) / kMaskY, a.K);
   };
-  const dim3 gq = grid(a.Wq, a.Hq), gp = grid((a.W + 3) / 4, a.H), b(kMaskX * kMaskY);
+  const dim3 gq = grid(a.Wq, a.Hq), b(kMaskX * kMaskY);
   if (a.factor % 4 == 0 && a.W % 4 == 0 &&
       (((uintptr_t)a.rgb | (uintptr_t)a.rgb_prev) & 3u) == 0)
     hipLaunchKernelGGL(mask_low_kernel<true>, gq, b, 0, s, a);
@@ -180,12 +173,11 @@ int launch_difference_masks(const MaskArgs &a, hipStream_t s) {
   if (int rc = check_hip(hipGetLastError(), "mask_low_kernel")) return rc;
   hipLaunchKernelGGL(mask_pool_kernel, gq, b, 0, s, a);
   if (int rc = check_hip(hipGetLastError(), "mask_pool_kernel")) return rc;
-  const bool wide = a.factor >= 4;
   const bool vec = a.W % 4 == 0 && (((uintptr_t)a.depth | (uintptr_t)a.prev | (uintptr_t)a.mask |
                                      (uintptr_t)a.filtered) & 15u) == 0;
-  void (*const up)(MaskArgs) = wide ? (vec ? mask_up_kernel<true, true> : mask_up_kernel<true, false>)
-                                    : (vec ? mask_up_kernel<false, true> : mask_up_kernel<false, false>);
-  hipLaunchKernelGGL(up, gp, b, 0, s, a);
+  void (*const up)(MaskArgs) = !vec ? mask_up_kernel<false, 1>
+                               : a.factor >= 4 ? mask_up_kernel<true, 4> : mask_up_kernel<false, 4>;
+  hipLaunchKernelGGL(up, grid(vec ? a.W / 4 : a.W, a.H), b, 0, s, a);
   return check_hip(hipGetLastError(), "mask_up_kernel");
 }
 
