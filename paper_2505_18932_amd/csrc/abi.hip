@@ -860,8 +860,9 @@ int tsdf_view_table(const gg_camera *src, int32_t K, const float *depth,
   if (!depth) return fail(GG_ERR_INVALID, "%s: NULL array argument", N);
   const TsdfLayout L = tsdf_layout(K, src[0].width, src[0].height, prm->num_bins, false);
   if (int rc = check_ws(ws, ws_bytes, L.base, N)) return rc;
-  return build_view_table(src, K, depth, prm, L, (char *)ws, cells_of(L, (char *)ws, ws_bytes),
-                          (hipStream_t)stream);
+  // (no fusion reads the ranges of one or two views: fuse_ranges)
+  uint32_t *cells = K > 2 ? cells_of(L, (char *)ws, ws_bytes) : nullptr;
+  return build_view_table(src, K, depth, prm, L, (char *)ws, cells, (hipStream_t)stream);
 }
 
 // depth NULL: the view table and bins are already in ws (tsdf_view_table).
