@@ -459,11 +459,10 @@ int tsdf_integrate_backward(const gg_camera *src, int32_t K, const float *depth,
 /* ---------------------------------------------------------------------------
  * Batched path: many target views of uneven resolution, view count and bin
  * count (each with its own inputs, cameras, parameters, volume and outputs)
- * fused by kernels over per-phase work lists (persistent ones for the splat
- * binning, one workgroup per tile for the others) in one hipGraph launch.
- * Every output is
- * bitwise identical to the plain calls (splat_views + tsdf_integrate with
- * fused extraction) on the same item, for any tuning.
+ * fused by kernels over per-phase work lists, one workgroup per entry, in one
+ * hipGraph launch.  Every output is bitwise identical to the plain calls
+ * (splat_views + tsdf_integrate with fused extraction) on the same item, for
+ * any tuning.
  * ------------------------------------------------------------------------- */
 typedef struct gg_batch_item {
   const gg_camera *src;         /* [host] K source cameras, one size per item        */

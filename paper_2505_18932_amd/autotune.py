@@ -6,10 +6,10 @@ caches the winner per GPU architecture and workload class in a JSON file
 next to this module (``tuning_cache.json``):
 
 * plain path: the band width of the fusion's tile order for a (K, D, width,
-  height) class: a launch shape the caller passes with each call (``tuning=`` of the volume calls, the C ABI's
-  ``gg_volume_tuning``); nothing is set process-wide;
-* batched path: (resident workgroups per compute unit of the persistent splat
-  binning, graph branches) for a batch signature.
+  height) class: a launch shape the caller passes with each call (``tuning=``
+  of the volume calls, the C ABI's ``gg_volume_tuning``); nothing is set
+  process-wide;
+* batched path: the graph's branches for a batch signature.
 """
 from __future__ import annotations
 
@@ -131,7 +131,7 @@ def batch_signature(items):
 
 def tune_batch(items, reps=3, use_cache=True):
     """Best (pixels_per_block, blocks_per_cu, bins_per_thread, branches) for this batch (one plan per
-    candidate over the same buffers, each closed before the next).
+    candidate over the same buffers, each closed before the next); only the branches vary.
     Returns (tuning, {candidate: ms})."""
     key = batch_signature(items)
     cache = _load()

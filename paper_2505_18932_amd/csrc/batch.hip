@@ -35,8 +35,8 @@ __global__ void batch_bins_kernel(const BatchItem *__restrict__ items) {
 // tile: their lists hold far more entries than the device holds workgroups,
 // so the dispatcher balances them as well as a work queue would, and gives
 // the two branches' workgroups their turns as others end (measured, six items
-// of 1280 x 720 to 1920 x 1080 with the binning in persistent workgroups, which
-// kept the fusion's out: 2225 us, 1401 now).  Entries go to the XCDs in
+// of 480 x 270 to 1280 x 720: 2225 us with the binning in persistent
+// workgroups, which kept the fusion's out, 1521 without).  Entries go to the XCDs in
 // contiguous parts (xcd_tile), so the tiles in flight on an XCD are
 // neighbours in the list and share the lines in its L2.
 __global__ __launch_bounds__(256) void batch_conf_kernel(const BatchItem *__restrict__ items,

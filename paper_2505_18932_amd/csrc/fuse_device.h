@@ -28,7 +28,6 @@ constexpr int kFuseMaxWaves = 16;   // of a workgroup (LDS of slabs: 79 KB)
 // four, where a slab is one 128-byte line of each pixel if D is a multiple of
 // 32.  The more workgroups share a compute unit, the better they hide each
 // other's latencies and barriers (measured, video: 517 us with eight, 447 us
-// with four; 640 x 400 K=4 D=100: 139 us with thirteen and a single slab, 95
 // with four).  Launches of no more workgroups than run at once take eight or
 // sixteen: their slabs would run one after the other beside idle wavefronts
 // (measured, 160 x 100 K=4 D=256: 54 us with four, 27 with sixteen).  Without a
@@ -508,8 +507,8 @@ struct SlabRows {
   }
 };
 
-// SlabDirect: 16-byte loads straight into LDS, which hold no registers (two
-// more wavefronts per SIMD).  Such a load puts a wavefront's 64 accesses one
+// SlabDirect: 16-byte loads straight into LDS, which hold no registers (five
+// wavefronts per SIMD instead of four).  Such a load puts a wavefront's 64 accesses one
 // after the other, so a block of 64 / (2 waves) pixels lies contiguous; for
 // the fusing lanes, one per pixel, the four-bin groups of a run are permuted
 // by the pixel (group g at slot g xor p), and blocks are 4 floats apart more:

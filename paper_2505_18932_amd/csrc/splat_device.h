@@ -1,5 +1,5 @@
 // Device functions of the z-buffered splat (§3.1, Suppl. A.3) shared by the
-// plain kernels (splat.hip) and the batched persistent kernels (batch.hip).
+// plain kernels (splat.hip) and the batched kernels (batch.hip).
 #pragma once
 
 #include <type_traits>

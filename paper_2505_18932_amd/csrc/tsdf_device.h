@@ -1,6 +1,6 @@
 // Device functions of the fusion (Suppl. A.1, A.2) shared by the plain
-// kernels (tsdf.hip) and the batched persistent kernels (batch.hip): one
-// definition, so both paths perform the identical operation sequence.
+// kernels (tsdf.hip) and the batched kernels (batch.hip): one definition, so
+// both paths perform the identical operation sequence.
 #pragma once
 
 #include <climits>

@@ -205,7 +205,8 @@ def volume_tuning(t):
     """A launch shape of the volume kernels, (pixels per workgroup, pixels per
     wavefront row, bins per thread[, band width in pixels of the fusion's
     tile order]) with 0 for a default, as the C record (or None: the
-    defaults)."""
+    defaults).  Only the band width shapes a launch; the others are checked,
+    and the bins per thread set the alignment that the volumes must have."""
     if t is None:
         return None
     if isinstance(t, L.GGVolumeTuning):
