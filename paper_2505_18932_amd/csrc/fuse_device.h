@@ -97,6 +97,7 @@ __host__ __device__ constexpr int form_waves(int f) { return f & kFormWindows ? 
 // The bins of which one window holds a whole row in LDS, and of which two workgroups still fit a
 // compute unit.
 constexpr int kFuseWhole = 312, kFuseWholeTwice = 156;
+constexpr uint32_t kFuseCuLds = 160u << 10;  // LDS of a compute unit
 
 // Whether a launch without a carry, whose bins are not whole lines, goes by windows instead of
 // slabs (integrate_windows).  Measured, slabs and windows: 1920 x 1080 K=1 D=100 831 and 351 us,
@@ -121,7 +122,10 @@ struct FuseShape {
 // views then take windows of 64 bins, three workgroups (1280 x 720 D=200 K=4 734 and 566, K=2 580
 // and 461; K=1 446 and 452; single floats of D=233 K=4 821 and 1065: one window).  Small launches
 // take as many wavefronts as run at once, few bins a wavefront per chunk (240 x 150 K=4 D=16 with
-// one 18.4 us, with two 14.9).
+// one 18.4 us, with two 14.9), in rounds of as many chunks each: 333 x 200 K=4 D=48 with five, one
+// chunk left for a second round, 29.4 us, with three 25.4; 240 x 150 K=4 D=100 29.0 with ten, 25.5
+// with eight.  But where two rounds of workgroups share the LDS, the most (240 x 150 K=8 D=108 38.2
+// with ten, 41.3 with eight).
 __host__ inline FuseShape fuse_shape(int form, int K, int D, uint32_t nblocks) {
   FuseShape s{fuse_waves(D, nblocks, form_direct(form), (form & kFormCarry) != 0), 0, 0u, 0};
   s.lds = FuseLds::bytes(s.waves);
@@ -132,7 +136,14 @@ __host__ inline FuseShape fuse_shape(int form, int K, int D, uint32_t nblocks) {
       const int rounds = (chunks + kFuseMaxWaves - 1) / kFuseMaxWaves;
       s.waves = D > 64 && D <= 108 ? 8 : D > 64 && !more ? 12 : (chunks - 1) / (rounds > 2 ? rounds : 2) + 1;
       // all that run at once, and a chunk each where there are few
-      const int room = (int)(256u * 24u / nblocks), least = D <= 24 ? chunks : (room < chunks ? room : chunks);
+      const int room = (int)(256u * 24u / nblocks);
+      int least = D <= 24 ? chunks : (room < chunks ? room : chunks);
+      // equal rounds, if the LDS has room for all workgroups at once
+      const uint32_t lds = (uint32_t)sizeof(float) * 2u * kFusePix * (uint32_t)(D + 1);
+      if (least > 0 && least < chunks && nblocks <= 256u * (kFuseCuLds / lds)) {
+        const int r = (chunks - 1) / least + 1;
+        least = (chunks - 1) / r + 1;
+      }
       if (s.waves < least) s.waves = least;
     }
     s.span = kFuseBins * chunks;

@@ -45,3 +45,10 @@ def test_windows_match_oracle(w, h, k, bins, f_off, w_off):
     gg.tsdf_integrate(c["src"], depth, c["tgt"], c["tsdf"], F=F, W=W, extract=False, tuning=(0, 0, 1, 0))
     assert torch.equal(F.view(torch.int32), got[0].view(torch.int32))
     assert torch.equal(W.view(torch.int32), got[1].view(torch.int32))
+
+
+# small launches whose chunks the wavefronts take in equal rounds, and where the LDS leaves them uneven
+@pytest.mark.parametrize("w,h,k,bins", [(333, 200, 2, 48), (300, 188, 1, 52), (333, 201, 1, 57), (240, 150, 3, 100),
+                                        (280, 180, 1, 60), (240, 150, 2, 108)])
+def test_windows_in_equal_rounds(w, h, k, bins):
+    test_windows_match_oracle(w, h, k, bins, 0, 0)
