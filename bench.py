@@ -724,13 +724,13 @@ def main():
     ap.add_argument("--no-ewa", action="store_true")
     ap.add_argument("--no-paper-shape", action="store_true")
     ap.add_argument("--batch-tuning", default="",
-                    help="batched plan 'threads_per_workgroup,blocks_per_cu' instead of autotuning "
-                         "(profiling runs pin what the timed runs pick)")
+                    help="batched plan '0,0,0,branches' instead of autotuning (1 or 2 branches of the graph; "
+                         "the other fields shape nothing)")
     ap.add_argument("--streams", type=int, default=2, choices=(1, 2),
                     help="2: the splat on its own stream, overlapping the fusion; 1: one stream")
     ap.add_argument("--tile", default="",
-                    help="fusion launch shape 'pixels_per_block,pixels_per_row,bins_per_thread' "
-                         "instead of autotuning (profiling runs pin the shape the timed runs pick)")
+                    help="fusion tuning '0,0,0,band_width' instead of autotuning (0: the library's "
+                         "choice; the other fields shape nothing)")
     ap.add_argument("--procs", type=int, default=0,
                     help="input-generation worker processes (0: min(16, cores))")
     ap.add_argument("--copy-calibration", type=int, default=0,
